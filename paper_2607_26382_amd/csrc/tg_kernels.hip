@@ -265,206 +265,281 @@ __global__ __launch_bounds__(256) void k_nodeblock(const ProbDesc* __restrict__ 
   }
 }
 
-// Coarsest level: assemble the dense free-DOF matrix, Cholesky-factor it and
-// form the explicit inverse (one workgroup per problem).
-__device__ __forceinline__ int coarse_free_index(const LevelDesc& L, int node, int c) {
-  const int i = node % L.NX, t = node / L.NX;   // t = j + NY k
-  return i == 0 ? -1 : 3 * ((L.NX - 1) * t + (i - 1)) + c;
+// Node coordinates and component of a free DOF of the coarsest level, one byte
+// each (i, j, k, component); a level of at most TG_MAX_COARSE free DOFs has
+// fewer than 256 nodes in every dimension.
+__device__ __forceinline__ int coarse_dof(const LevelDesc& L, int r) {
+  const int nxm = L.NX - 1, f = r / 3, t = f / nxm, k = t / L.NY;
+  return (f - t * nxm + 1) | (t - k * L.NY) << 8 | k << 16 | (r - 3 * f) << 24;
+}
+// Entry (r, c) of the coarsest level's assembled free-DOF matrix (dr, dc: the
+// two DOFs' coarse_dof): the sum of the element entries that couple them, over
+// the up to eight elements both nodes share, in ascending element order; the
+// unit matrix beyond n.  The eight loads are issued together (absent elements
+// read entry 0).
+__device__ __forceinline__ double coarse_entry(const ProbDesc& P, const LevelDesc& L, bool fine, int n, int r,
+                                               int c, int dr, int dc) {
+  const bool pad = r >= n || c >= n;
+  const double unit = pad && r == c ? 1.0 : 0.0;
+  const int i = dr & 255, j = (dr >> 8) & 255, kr = (dr >> 16) & 255, cr = dr >> 24, cc = dc >> 24;
+  const int di = (dc & 255) - i, dj = ((dc >> 8) & 255) - j, dk = ((dc >> 16) & 255) - kr;
+  const bool near = !pad && di >= -1 && di <= 1 && dj >= -1 && dj <= 1 && dk >= -1 && dk <= 1;
+  if (!__any(near)) return unit;
+  const auto* Kg = gp(fine ? P.Ke64 : (const double*)L.Kel64);
+  const auto* Eg = gp((const double*)P.E64);
+  double k[8], E[8];
+  bool in[8];
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    // the element in which node (i, j, kr) is corner a; the other node's corner
+    const int ax = a & 1, ay = (a >> 1) & 1, az = a >> 2;
+    const int bx = ax + di, by = ay + dj, bz = az + dk;
+    const int ex = i - ax, ey = j - ay, ez = kr - az;   // ex >= 0: i >= 1
+    in[a] = near && bx >= 0 && bx <= 1 && by >= 0 && by <= 1 && bz >= 0 && bz <= 1 && ex < L.ex && ey >= 0 &&
+            ey < L.ey && ez >= 0 && ez < L.ez;
+    const int e = in[a] ? ex + L.ex * (ey + L.ey * ez) : 0;
+    const int q = in[a] ? (3 * a + cr) * 24 + 3 * (bx + 2 * by + 4 * bz) + cc : 0;
+    k[a] = Kg[fine ? q : 576 * e + q];
+    E[a] = fine ? Eg[e] : 1.0;
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int a = 7; a >= 0; --a) s += in[a] ? E[a] * k[a] : 0.0;
+  return pad ? unit : s;
 }
 
-__global__ __launch_bounds__(256) void k_coarse_factor(const ProbDesc* __restrict__ probs,
-                                                       const int2* __restrict__ work, int* bad, int nmin) {
-  const int2 wi = work[blockIdx.x];
-  const ProbDesc& P = probs[wi.x];
-  const int l = P.nlev - 1;
-  const LevelDesc& L = P.lv[l];
-  const int n = P.ncoarse;
-  if (n == 0 || n < nmin) return;  // no direct-solvable coarsest level, or one k_coarse_factor_lds took
-  double* A = P.Cwork;             // n x n, row-major; lower triangle -> L
-  double* X = P.Cwork + (long long)n * n;
-  for (int q = threadIdx.x; q < n * n; q += blockDim.x) A[q] = 0.0;
-  __syncthreads();
-  const int ne = L.ex * L.ey * L.ez;
-  for (int e = 0; e < ne; ++e) {
-    const int ex = e % L.ex, ey = (e / L.ex) % L.ey, ez = e / (L.ex * L.ey);
-    for (int q = threadIdx.x; q < 576; q += blockDim.x) {
-      const int r = q / 24, c = q % 24;
-      const int a = r / 3, b = c / 3;
-      const int na = (ex + (a & 1)) + L.NX * ((ey + ((a >> 1) & 1)) + L.NY * (ez + ((a >> 2) & 1)));
-      const int nb = (ex + (b & 1)) + L.NX * ((ey + ((b >> 1) & 1)) + L.NY * (ez + ((b >> 2) & 1)));
-      const int fr = coarse_free_index(L, na, r % 3), fc = coarse_free_index(L, nb, c % 3);
-      if (fr < 0 || fc < 0) continue;
-      const double v = (l == 0) ? P.E64[e] * P.Ke64[q] : L.Kel64[(long long)e * 576 + q];
-      A[fr * n + fc] += v;         // distinct (fr, fc) within one element
-    }
-    __syncthreads();
+// Memory ordering between the lanes of one wave
+// (the wave is in lockstep; the fence keeps the compiler and the LDS queue
+// from moving a lane's reads above another lane's writes)
+#define TG_WAVE_SYNC()                                       \
+  do {                                                       \
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   \
+    __builtin_amdgcn_wave_barrier();                         \
+  } while (0)
+
+// One 64-bit value of lane `lane` (a constant), in every lane of the wave.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(w.x, lane),
+                                              __builtin_amdgcn_readlane(w.y, lane)));
+}
+// Lane K of each row of 16 lanes, in every lane of that row.
+template <int K>
+__device__ __forceinline__ double row_value(double v) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, w.x, 0x150 + K, 0xf, 0xf, false),
+                                              __builtin_amdgcn_update_dpp(0, w.y, 0x150 + K, 0xf, 0xf, false)));
+}
+
+// Pivot K of the unit-lower elimination of a 16 x 16 symmetric block held by
+// one wave (lane l: row l % 16, columns 4 (l / 16) + q): with m = the unit
+// matrix at the start, all sixteen pivots leave m = M, the inverse of the unit
+// lower factor of A = M^-1 diag(p) M^-T.  pinv: 1 / p of this lane's row.
+template <int K>
+__device__ __forceinline__ void ldl_pivot(double* a, double* m, int lane, double& pinv, bool& ok) {
+  const int row = lane & 15;
+  const double p = lane_value(a[K & 3], K + 16 * (K >> 2));
+  ok = ok && p > 0.0;
+  const double d = 1.0 / p;
+  if (row == K) pinv = d;
+  const double col = __shfl(a[K & 3], row + 16 * (K >> 2), 64);   // a[row][K]
+  const double f = row > K ? col * d : 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    a[q] -= f * row_value<K>(a[q]);
+    m[q] -= f * row_value<K>(m[q]);
   }
-  // right-looking Cholesky, lower triangle
-  __shared__ double piv;
-  for (int k = 0; k < n; ++k) {
-    if (threadIdx.x == 0) {
-      const double d = A[k * n + k];
-      if (!(d > 0.0)) atomicOr(bad + wi.x, 2);
-      piv = sqrt(fmax(d, 1e-300));
-      A[k * n + k] = piv;
-    }
-    __syncthreads();
-    for (int r = k + 1 + threadIdx.x; r < n; r += blockDim.x) A[r * n + k] /= piv;
-    __syncthreads();
-    for (int q = threadIdx.x; q < (n - k - 1) * (n - k - 1); q += blockDim.x) {
-      const int r = k + 1 + q / (n - k - 1), c = k + 1 + q % (n - k - 1);
-      if (c <= r) A[r * n + c] -= A[r * n + k] * A[c * n + k];
-    }
-    __syncthreads();
-  }
-  // inverse: column q of X solves L L^T x = e_q (one column per thread)
-  for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    for (int r = 0; r < n; ++r) {     // forward: L y = e_q
-      double s = (r == q) ? 1.0 : 0.0;
-      for (int c = q; c < r; ++c) s -= A[r * n + c] * X[c * n + q];
-      X[r * n + q] = (r < q) ? 0.0 : s / A[r * n + r];
-    }
-    for (int r = n - 1; r >= 0; --r) {   // backward: L^T x = y
-      double s = X[r * n + q];
-      for (int c = r + 1; c < n; ++c) s -= A[c * n + r] * X[c * n + q];
-      X[r * n + q] = s / A[r * n + r];
-    }
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < n * n; q += blockDim.x) {
-    const int r = q / n, c = q % n;
-    // symmetrize the explicit inverse
-    const double v = 0.5 * (X[r * n + c] + X[c * n + r]);
-    P.Cinv64[q] = v;
-    P.Cinv32[q] = (float)v;
+}
+template <int K = 0>
+__device__ __forceinline__ void ldl_block(double* a, double* m, int lane, double& pinv, bool& ok) {
+  if constexpr (K < 16) {
+    ldl_pivot<K>(a, m, lane, pinv, ok);
+    ldl_block<K + 1>(a, m, lane, pinv, ok);
   }
 }
 
-// The same coarsest-level set-up held in LDS, for coarsest levels whose
-// matrix fits (n^2 + 2 n doubles): the assembled matrix is inverted in place
-// by Gauss-Jordan elimination without pivoting (its pivots are the diagonal
-// entries of successive Schur complements, positive for an SPD matrix), all
-// n^2 updates of a step in parallel; the explicit inverse is symmetrized as
-// in k_coarse_factor.  A non-positive pivot flags the problem.
-#define CF_THREADS 1024
-#define CF_REG 16   // register form: rows per thread (n <= 128)
-__global__ __launch_bounds__(CF_THREADS) void k_coarse_factor_lds(const ProbDesc* __restrict__ probs,
-                                                                  const int2* __restrict__ work, int* bad,
-                                                                  int nmax) {
+// Coarsest level's explicit inverse, one workgroup per problem: the assembled
+// free-DOF matrix, padded with the unit matrix to T x T tiles of 16, is swept
+// block pivot by block pivot.  With A_KK = M^-1 diag(p) M^-T, G_I = A_IK
+// (= A_KI^T) and G'_I = G_I M^T:
+//   A_IJ -= G'_I diag(1/p) G'_J^T,  A_IK <- G'_I diag(1/p) M,
+//   A_KK <- -M^T diag(1/p) M,
+// which keeps the matrix symmetric, so only the tiles I >= J are held, and
+// leaves -A^-1.  (The factored form of A_KK^-1 keeps the Schur complements as
+// accurate as a Cholesky elimination; its explicit inverse would not.)  No
+// pivoting: the pivots are diagonal entries of successive Schur complements,
+// positive for an SPD matrix (a non-positive one flags the problem).
+// What bounds it is the chain of n pivots: each 16 of them are done by one
+// wave in registers (row and column of the pivot by lane moves), beside the
+// other waves' matrix-core update of the previous block, so a block pivot
+// costs two barriers.  One element-by-element Gauss-Jordan pivot per barrier
+// took 170 us at n = 108, and the global-memory Cholesky that n > 141 used
+// took 22.9 ms at n = 288; this form takes 47 and 324 us.
+// LDS = true holds the tiles in LDS (n <= CI_LDS_N, where they fit beside the
+// panel); otherwise they live in the problem's work array, which one
+// workgroup's waves keep in cache.
+// Lane layouts of v_mfma_f64_16x16x4 (measured on gfx950): A[i][k] and
+// B[k][j] at lane i (j) + 16 k; D[i][j] at lane 16 (i % 4) + j, element i / 4.
+// A tile is stored in the D layout; slot s of lane group c is k = c + 4 s in
+// every product.
+#define CI_THREADS 1024
+#define CI_LDS_N 144    // 45 tiles (92 KB) and a 20 KB panel
+#define CI_LD 18        // panel row stride (16 columns, padded)
+#define CI_M (16 * CI_LD + 16)   // M and 1 / p of a block pivot
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__host__ __device__ inline size_t ci_lds_words(int n, bool tiles_in_lds) {
+  const int T = (n + 15) / 16;
+  // panel, two M blocks, tile order and DOF coordinates (32-bit each), tiles
+  return (size_t)16 * T * CI_LD + 2 * CI_M + (T * (T + 1) / 2 + 16 * T + 1) / 2 +
+         (tiles_in_lds ? (size_t)T * (T + 1) / 2 * 256 : 0);
+}
+
+template <bool LDS>
+__global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* __restrict__ probs,
+                                                               const int2* __restrict__ work, int* bad, int nlo,
+                                                               int nhi) {
   extern __shared__ double smem[];
   const int2 wi = work[blockIdx.x];
   const ProbDesc& P = probs[wi.x];
-  const int l = P.nlev - 1;
-  const LevelDesc& L = P.lv[l];
   const int n = P.ncoarse;
-  if (n == 0 || n > nmax) return;   // larger coarsest levels: k_coarse_factor
-  double* A = smem;                  // n x n, row-major
-  double* rowk = smem + n * n;       // pivot row, scaled
-  double* colk = rowk + n;           // pivot column
-  for (int q = threadIdx.x; q < n * n; q += blockDim.x) A[q] = 0.0;
+  if (n == 0 || n < nlo || n > nhi) return;   // no direct coarsest level, or the other form's size
+  const LevelDesc& L = P.lv[P.nlev - 1];
+  const bool fine = P.nlev == 1;
+  const int T = (n + 15) >> 4, NT = T * (T + 1) / 2;
+  double* G = smem;                       // panel: row r, column k at r CI_LD + k
+  double* sM = G + 16 * T * CI_LD;        // M, same row stride, then 1 / p; of even and odd block pivots
+  int* sT = (int*)(sM + 2 * CI_M);      // tile u in column order: I | J << 8
+  int* sN = sT + NT;                      // coarse_dof of every free DOF
+  double* A = LDS ? sM + 2 * CI_M + (NT + 16 * T + 1) / 2 : P.Cwork;
+  // (wave: uniform, so that tile indices and addresses stay scalar)
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lj = lane & 15, lc = lane >> 4;
+  constexpr int NW = CI_THREADS / 64;
+  for (int q = threadIdx.x; q < T * T; q += CI_THREADS) {
+    const int J = q / T, I = q - J * T;
+    if (I >= J) sT[J * T - J * (J - 1) / 2 + I - J] = I | J << 8;
+  }
+  for (int q = threadIdx.x; q < 16 * T; q += CI_THREADS) sN[q] = coarse_dof(L, q);
   __syncthreads();
-  const int ne = L.ex * L.ey * L.ez;
-  for (int e = 0; e < ne; ++e) {
-    const int ex = e % L.ex, ey = (e / L.ex) % L.ey, ez = e / (L.ex * L.ey);
-    for (int q = threadIdx.x; q < 576; q += blockDim.x) {
-      const int r = q / 24, c = q % 24;
-      const int a = r / 3, b = c / 3;
-      const int na = (ex + (a & 1)) + L.NX * ((ey + ((a >> 1) & 1)) + L.NY * (ez + ((a >> 2) & 1)));
-      const int nb = (ex + (b & 1)) + L.NX * ((ey + ((b >> 1) & 1)) + L.NY * (ez + ((b >> 2) & 1)));
-      const int fr = coarse_free_index(L, na, r % 3), fc = coarse_free_index(L, nb, c % 3);
-      if (fr < 0 || fc < 0) continue;
-      const double v = (l == 0) ? P.E64[e] * P.Ke64[q] : L.Kel64[(long long)e * 576 + q];
-      A[fr * n + fc] += v;         // distinct (fr, fc) within one element
+  auto tile_of = [&](int u) -> int { return __builtin_amdgcn_readfirstlane(sT[u]); };
+  for (int u = wave; u < NT; u += NW) {
+    const int ij = tile_of(u), I = ij & 255, J = ij >> 8, t = I * (I + 1) / 2 + J;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * I + lc + 4 * v, c = 16 * J + lj, hi = max(r, c), lo = min(r, c);
+      A[t * 256 + 64 * v + lane] = coarse_entry(P, L, fine, n, hi, lo, sN[hi], sN[lo]);
+    }
+  }
+  __syncthreads();
+  // tile entry (i, j) of tile t
+  auto at = [&](int t, int i, int j) -> double { return A[t * 256 + 64 * (i >> 2) + 16 * (i & 3) + j]; };
+  // wave 0: M and 1 / p of the block pivot K from tile (K, K), to LDS
+  auto factor = [&](int K) {
+    double a[4], m[4], pinv = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      a[q] = at(K * (K + 1) / 2 + K, lj, 4 * lc + q);
+      m[q] = lj == 4 * lc + q ? 1.0 : 0.0;
+    }
+    bool ok = true;
+    ldl_block(a, m, lane, pinv, ok);
+    if (!ok && lane == 0) atomicOr(bad + wi.x, 2);
+    double* o = sM + (K & 1) * CI_M;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[lj * CI_LD + 4 * lc + q] = m[q];
+    if (lc == 0) o[16 * CI_LD + lj] = pinv;
+  };
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  auto mul = [&](const f64x4& a, const f64x4& b, f64x4 c) -> f64x4 {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+    return c;
+  };
+  auto rows = [&](const double* X) -> f64x4 {   // X[lj][lc + 4 s]
+    f64x4 g;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) g[s] = X[lj * CI_LD + lc + 4 * s];
+    return g;
+  };
+  if (wave == 0) factor(0);
+  __syncthreads();
+  for (int K = 0; K < T; ++K) {
+    const double* M = sM + (K & 1) * CI_M;
+    const f64x4 Mr = rows(M);           // M[lj][lc + 4 s]
+    f64x4 Mc, ip;                       // M[lc + 4 s][lj], 1 / p[lc + 4 s]
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Mc[s] = M[(lc + 4 * s) * CI_LD + lj];
+      ip[s] = M[16 * CI_LD + lc + 4 * s];
+    }
+    // panel G' = G M^T, G = column K of the symmetric matrix; each wave turns
+    // its own tiles into rows through their places in the panel
+    for (int I = wave; I < T; I += NW) {
+      const int t = I >= K ? I * (I + 1) / 2 + K : K * (K + 1) / 2 + I;
+      double* X = G + 16 * I * CI_LD;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const double x = A[t * 256 + 64 * v + lane];   // entry (lc + 4 v, lj) of the stored tile
+        if (I >= K)
+          X[(lc + 4 * v) * CI_LD + lj] = x;
+        else
+          X[lj * CI_LD + lc + 4 * v] = x;
+      }
+      TG_WAVE_SYNC();
+      const f64x4 g = mul(rows(X), Mr, zero);
+      TG_WAVE_SYNC();
+#pragma unroll
+      for (int v = 0; v < 4; ++v) X[(lc + 4 * v) * CI_LD + lj] = g[v];
+    }
+    __syncthreads();
+    auto tile = [&](int t) -> f64x4 {
+      f64x4 c;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) c[v] = A[t * 256 + 64 * v + lane];
+      return c;
+    };
+    auto update = [&](int t, int I, int J, f64x4 c) {   // c: the tile's old value
+      const f64x4 gi = rows(G + 16 * I * CI_LD), gj = rows(G + 16 * J * CI_LD);
+      if (I != K && J != K) c = mul(-gi, gj * ip, c);   // A_IJ - G'_I diag(1/p) G'_J^T
+      else if (I != K) c = mul(gi * ip, Mc, zero);      // G'_I diag(1/p) M
+      else if (J != K) c = mul(Mc * ip, gj, zero);      // its transpose for a tile left of the diagonal
+      else c = -mul(Mc * ip, Mc, zero);                 // -M^T diag(1/p) M
+#pragma unroll
+      for (int v = 0; v < 4; ++v) A[t * 256 + 64 * v + lane] = c[v];
+    };
+    const int tn = (K + 1) * (K + 2) / 2 + K + 1;       // tile (K + 1, K + 1)
+    if (wave == 0) {
+      if (K + 1 < T) {
+        update(tn, K + 1, K + 1, tile(tn));
+        TG_WAVE_SYNC();                                 // the tile is read back in another layout
+        factor(K + 1);
+      }
+    } else {
+      const int u0 = (wave - 1) * NT / (NW - 1), u1 = wave * NT / (NW - 1);
+      f64x4 next = zero;
+      int ij = 0, t = 0;
+      auto fetch = [&](int u) {   // the next tile's values are loaded one update ahead
+        ij = tile_of(u);
+        const int I = ij & 255;
+        t = I * (I + 1) / 2 + (ij >> 8);
+        next = tile(t);
+      };
+      if (u0 < u1) fetch(u0);
+      for (int u = u0; u < u1; ++u) {
+        const f64x4 c = next;
+        const int I = ij & 255, J = ij >> 8, tu = t;
+        if (u + 1 < u1) fetch(u + 1);
+        if (tu == tn) continue;                         // wave 0's
+        update(tu, I, J, c);
+      }
     }
     __syncthreads();
   }
-  // Register form: thread t holds column j = t mod n of the rows t / n +
-  // q rpp (rpp = rows per pass, q < cm).  Each step publishes the pivot
-  // column and row through one of two alternating LDS buffers (one barrier
-  // per step); the column is stored in slot order, row i at
-  // (i mod rpp) cm + i / rpp, so a thread's rows are contiguous.  Every
-  // register takes the generic update a -= c_i r_j / p (unused ones too, on
-  // values never stored), then the holders of row k and of column k write
-  // their special values: the same operations as the LDS form below.
-  const int rpp = CF_THREADS / n;
-  const int cm = (n + rpp - 1) / rpp;
-  if (n >= 2 && cm <= CF_REG) {
-    const int t = threadIdx.x, j = t % n, i0 = t / n;
-    const bool act = t < rpp * n;
-    const int cnt = act ? (n - i0 + rpp - 1) / rpp : 0;
-    const int csz = rpp * cm + CF_REG, bsz = csz + n;   // column part (padded), buffer
-    const int cb = (act ? i0 : 0) * cm;                 // this thread's first slot
-    double a[CF_REG];
-#pragma unroll
-    for (int q = 0; q < CF_REG; ++q) a[q] = q < cnt ? A[(i0 + q * rpp) * n + j] : 0.0;
-    __syncthreads();   // A's storage now holds the pivot buffers
-    for (int k = 0; k < n; ++k) {
-      double* ck = smem + (k & 1) * bsz;
-      double* rk = ck + csz;
-      const bool rowk = act && k % rpp == i0, colk = act && j == k;
-      const int qk = k / rpp;
-      if (colk) {
-#pragma unroll
-        for (int q = 0; q < CF_REG; ++q)
-          if (q < cnt) ck[cb + q] = a[q];
-      }
-      if (rowk) {
-        double v = 0.0;
-#pragma unroll
-        for (int q = 0; q < CF_REG; ++q) v = q == qk ? a[q] : v;
-        rk[j] = v;
-      }
-      __syncthreads();
-      const double p = ck[(k % rpp) * cm + qk];
-      if (t == 0 && !(p > 0.0)) atomicOr(bad + wi.x, 2);
-      const double ip = 1.0 / p;
-      const double rj = rk[j] * ip;
-      double ci[CF_REG];
-#pragma unroll
-      for (int q = 0; q < CF_REG; ++q) ci[q] = ck[cb + q];
-#pragma unroll
-      for (int q = 0; q < CF_REG; ++q) a[q] -= ci[q] * rj;
-      if (rowk) {
-        const double v = colk ? ip : rj;
-#pragma unroll
-        for (int q = 0; q < CF_REG; ++q) a[q] = q == qk ? v : a[q];
-      }
-      if (colk) {
-#pragma unroll
-        for (int q = 0; q < CF_REG; ++q)
-          if (q < cnt && i0 + q * rpp != k) a[q] = -ci[q] * ip;
-      }
-    }
-    __syncthreads();   // every read of the last pivot buffers is done
-#pragma unroll
-    for (int q = 0; q < CF_REG; ++q)
-      if (q < cnt) A[(i0 + q * rpp) * n + j] = a[q];
-    __syncthreads();
-  } else {
-  for (int k = 0; k < n; ++k) {
-    const double p = A[k * n + k];
-    if (threadIdx.x == 0 && !(p > 0.0)) atomicOr(bad + wi.x, 2);
-    const double ip = 1.0 / p;
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
-      colk[j] = A[j * n + k];
-      rowk[j] = A[k * n + j] * ip;
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < n * n; q += blockDim.x) {
-      const int i = q / n, j = q - (q / n) * n;
-      if (i == k)
-        A[q] = (j == k) ? ip : rowk[j];
-      else if (j == k)
-        A[q] = -colk[i] * ip;
-      else
-        A[q] -= colk[i] * rowk[j];
-    }
-    __syncthreads();
-  }
-  }
-  for (int q = threadIdx.x; q < n * n; q += blockDim.x) {
-    const int r = q / n, c = q % n;
-    const double v = 0.5 * (A[r * n + c] + A[c * n + r]);
+  for (int q = threadIdx.x; q < n * n; q += CI_THREADS) {
+    const int r = max(q / n, q % n), c = min(q / n, q % n);
+    const int I = r >> 4, J = c >> 4, t = I * (I + 1) / 2 + J;
+    // (a diagonal tile holds both triangles, equal up to rounding)
+    const double v = I == J ? -0.5 * (at(t, r & 15, c & 15) + at(t, c & 15, r & 15)) : -at(t, r & 15, c & 15);
     P.Cinv64[q] = v;
     P.Cinv32[q] = (float)v;
   }
@@ -1169,15 +1244,6 @@ __global__ void k_arnoldi_(const ProbDesc* __restrict__ probs, const int2* __res
 // coefficients), replacing the tentative column and rotation of step j-1.
 // The first-pass coefficients of column j are h1 = [Q^T w ; q_j . w]; the
 // coefficients of sweep B go to tmp (see k_update2_).
-// LDS ordering between the lanes of the one wave that runs a scalar part
-// (the wave is in lockstep; the fence keeps the compiler and the LDS queue
-// from moving a lane's reads above another lane's writes)
-#define TG_WAVE_SYNC()                                       \
-  do {                                                       \
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   \
-    __builtin_amdgcn_wave_barrier();                         \
-  } while (0)
-
 __device__ void dcgs_a_wave(const ProbDesc& P, int p, const SmallOffs& o, int j, double* status_out) {
   // one wave: the column and the rotations are read in parallel and rotated
   // in LDS by lane 0 (a chain of register operations rather than of round
@@ -1505,53 +1571,28 @@ static double dofs0(const Batch* b) {
     if (_th) timer_end(_th, (double)(bytes_expr), s);   \
   } while (0)
 
-// Largest coarsest level (free DOFs) whose two packed triangles fit the
-// dynamic LDS the set-up kernel may take on the current device (the
-// device's per-workgroup limit less the kernel's static LDS), with the
-// kernel's limit raised to it once per device.
-static size_t coarse_lds_limit();
-// LDS doubles k_coarse_factor_lds needs for a coarsest level of n free
-// DOFs: the assembled matrix and two pivot rows (LDS form), or the two pivot
-// buffers of the register form when it applies.
-static size_t coarse_lds_words(int n) {
-  size_t w = (size_t)n * (n + 2);
-  const int rpp = CF_THREADS / n, cm = (n + rpp - 1) / rpp;
-  if (n >= 2 && cm <= CF_REG) w = std::max(w, (size_t)2 * (rpp * cm + CF_REG + n));
-  return w;
-}
-static int coarse_lds_n() {
-  const size_t lim = coarse_lds_limit();
-  int n = 0;
-  while (sizeof(double) * (size_t)(n + 1) * (n + 3) <= lim) ++n;   // (n + 1)^2 + 2 (n + 1)
-  return n;
-}
-static size_t coarse_lds_limit() {
-  static size_t lim[64] = {};
+// Raises the dynamic-LDS limit of the coarsest-inverse kernels on the current
+// device to what their largest problem takes, once per device.
+static int coarse_lds_raise() {
   static bool done[64] = {};
   static std::mutex mu;   // batches on several host threads
   std::lock_guard<std::mutex> lk(mu);
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  if (!done[dev]) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
-      (void)hipGetLastError();   // leave no error for the next launch check
-      v = 0;
-    }
-    size_t l = v > 1024 ? (size_t)v - 1024 : 0;
-    if (l && hipFuncSetAttribute((const void*)k_coarse_factor_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)l) != hipSuccess) {
-      (void)hipGetLastError();
-      l = std::min<size_t>(l, 65536 - 1024);
-    }
-    lim[dev] = l;
-    done[dev] = true;
-  }
-  return lim[dev];
+  TG_HIP(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64) return fail(TG_EINVAL, "device index out of range");
+  if (done[dev]) return TG_OK;
+  TG_HIP(hipFuncSetAttribute((const void*)k_coarse_inverse<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)(sizeof(double) * ci_lds_words(CI_LDS_N, true))));
+  TG_HIP(hipFuncSetAttribute((const void*)k_coarse_inverse<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)(sizeof(double) * ci_lds_words(TG_MAX_COARSE, false))));
+  done[dev] = true;
+  return TG_OK;
 }
 
 int k_set_density(Batch* b, hipStream_t s) {
   int* bad = b->flag_d;
+  const int rc = coarse_lds_raise();
+  if (rc) return rc;
   TG_HIP(hipMemsetAsync(bad, 0, sizeof(int) * b->n, s));
   TG_TIMED(TG_KT_SETUP, 0, {
     if (b->elem[0].n) k_young<<<nblk(b->elem[0]), 256, 0, s>>>(b->desc_d, b->elem[0].ptr, b->p, bad);
@@ -1563,24 +1604,20 @@ int k_set_density(Batch* b, hipStream_t s) {
     for (int l = 0; l < b->maxlev; ++l)
       if (b->node[l].n) k_nodeblock<<<nblk(b->node[l]), 256, 0, s>>>(b->desc_d, b->node[l].ptr, l);
     if (b->prob.n) {
-      // which kernel sets up a problem depends only on its own coarsest size
-      // and the device, so a problem gets the same inverse alone or batched
-      const int nlds = coarse_lds_n();
-      int nmax = 0, nmin = INT_MAX;
+      // which form inverts a problem's coarsest matrix depends only on its own
+      // size, so a problem gets the same inverse alone or batched
+      int n_lds = 0, n_big = 0;
       for (int p : b->active) {
         const int n = b->grids[p]->ncoarse;
-        if (n > 0) nmax = std::max(nmax, n), nmin = std::min(nmin, n);
+        if (n <= CI_LDS_N) n_lds = std::max(n_lds, n);
+        else n_big = std::max(n_big, n);
       }
-      if (nmin <= nlds) {
-        size_t words = 0;
-        for (int p : b->active) {
-          const int n = b->grids[p]->ncoarse;
-          if (n > 0 && n <= nlds) words = std::max(words, coarse_lds_words(n));
-        }
-        k_coarse_factor_lds<<<nblk(b->prob), CF_THREADS, sizeof(double) * words, s>>>(b->desc_d, b->prob.ptr,
-                                                                                        bad, nlds);
-      }
-      if (nmax > nlds) k_coarse_factor<<<nblk(b->prob), 256, 0, s>>>(b->desc_d, b->prob.ptr, bad, nlds + 1);
+      if (n_lds)
+        k_coarse_inverse<true><<<nblk(b->prob), CI_THREADS, sizeof(double) * ci_lds_words(n_lds, true), s>>>(
+            b->desc_d, b->prob.ptr, bad, 1, CI_LDS_N);
+      if (n_big)
+        k_coarse_inverse<false><<<nblk(b->prob), CI_THREADS, sizeof(double) * ci_lds_words(n_big, false), s>>>(
+            b->desc_d, b->prob.ptr, bad, CI_LDS_N + 1, TG_MAX_COARSE);
     }
   });
   return check_launch("set_density kernels");
