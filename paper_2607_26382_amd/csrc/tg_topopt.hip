@@ -8,10 +8,10 @@
 // reduction Sec. 5.2 names as untested), or fixed without acceptance test
 // (the controls of Sec. 4.1.2).
 //
-// Filter, projection and OC kernels are elementwise or small stencils over
-// the element grid (x fastest); every sum runs in a fixed order.  The
-// bisection and the loop run on the host around them: each step needs one
-// scalar (the volume, the largest change) back.
+// Every kernel here is a small stencil over the element grid (x fastest); a
+// workgroup stages its tile of elements and their halo in LDS.  Sums run in a
+// fixed order.  The bisection's decisions are taken on the device, several
+// multipliers per launch; the loop runs on the host around the kernels.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -26,125 +26,333 @@ namespace {
 constexpr int TO_BLOCK = 256;
 constexpr int TO_MAX_R = 3;       // stencil half-width: r_min < 4
 
-__device__ __forceinline__ void elem_ijk(long long e, int nx, int ny, int& i, int& j, int& k) {
-  i = (int)(e % nx);
-  const long long r = e / nx;
-  j = (int)(r % ny);
-  k = (int)(r / ny);
-}
+// Weights of the hat filter by squared distance |d|^2 (0 where r_min <= |d|)
+// and the sum of all of them in the order dz, dy, dx (W of an element whose
+// stencil lies inside the grid); passed to the kernels by value, so that the
+// weights come in scalar registers.
+struct Hat {
+  double wsum;
+  double w[3 * TO_MAX_R * TO_MAX_R + 1];
+};
 
-// sum_j w_ej a_j (b_j) / (sum_j w_ej) over the in-grid neighbours j of e,
-// w = r - |d| > 0, |d_i| <= R; the offset order is fixed.
-__device__ __forceinline__ void hat_sums(int i, int j, int k, int nx, int ny, int nz, int R, double r,
-                                         const double* a, double& s, double& W) {
-  s = 0.0;
-  W = 0.0;
-  for (int dz = -R; dz <= R; ++dz)
-    for (int dy = -R; dy <= R; ++dy)
-      for (int dx = -R; dx <= R; ++dx) {
-        const double w = r - sqrt((double)(dx * dx + dy * dy + dz * dz));
-        const int ii = i + dx, jj = j + dy, kk = k + dz;
-        if (w <= 0 || ii < 0 || ii >= nx || jj < 0 || jj >= ny || kk < 0 || kk >= nz) continue;
-        W += w;
-        if (a) s += w * a[ii + (long long)nx * (jj + (long long)ny * kk)];
-      }
-}
+// Tile of 16 x 4 x 4 elements and its halo of R elements on every side.
+template <int R>
+struct Tile {
+  static constexpr int X = 16, Y = 4, Z = 4;
+  static constexpr int SX = X + 2 * R, SY = Y + 2 * R, SZ = Z + 2 * R, N = SX * SY * SZ;
+};
+static_assert(Tile<0>::X * Tile<0>::Y * Tile<0>::Z == TO_BLOCK, "one thread per element of a tile");
 
-// xt = H x (and, if beta > 0, xbar = project(xt), dxbar its derivative).
-__global__ __launch_bounds__(TO_BLOCK) void k_filter(const double* __restrict__ x, int nx, int ny, int nz,
-                                                     int R, double r, double beta, double eta,
-                                                     double* __restrict__ xt, double* __restrict__ xbar,
-                                                     double* __restrict__ dxbar) {
-  const long long n = (long long)nx * ny * nz;
-  for (long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x; e < n; e += (long long)gridDim.x * TO_BLOCK) {
-    int i, j, k;
-    elem_ijk(e, nx, ny, i, j, k);
-    double s, W;
-    hat_sums(i, j, k, nx, ny, nz, R, r, x, s, W);
-    const double v = s / W;
-    if (xt) xt[e] = v;
-    if (xbar) {
-      const double den = tanh(beta * eta) + tanh(beta * (1.0 - eta));
-      const double th = tanh(beta * (v - eta));
-      xbar[e] = fmin(1.0, fmax(0.0, (tanh(beta * eta) + th) / den));   // rounding stays in [0, 1]
-      if (dxbar) dxbar[e] = beta * (1.0 - th * th) / den;
-    }
-  }
-}
+struct Dims {
+  int nx, ny, nz;
+  int tx, ty, tz;                 // tiles per dimension
+  long long n;
+};
 
-// y_j = sum_e w_ej a_e b_e / W_e (b may be NULL: 1), W_e recomputed for each
-// neighbour e (the stencil is symmetric, so e runs over j's own stencil).
-__global__ __launch_bounds__(TO_BLOCK) void k_filter_adj(const double* __restrict__ a,
-                                                         const double* __restrict__ b, int nx, int ny,
-                                                         int nz, int R, double r, double* __restrict__ y) {
-  const long long n = (long long)nx * ny * nz;
-  for (long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x; e < n; e += (long long)gridDim.x * TO_BLOCK) {
-    int i, j, k;
-    elem_ijk(e, nx, ny, i, j, k);
-    double acc = 0.0;
-    for (int dz = -R; dz <= R; ++dz)
-      for (int dy = -R; dy <= R; ++dy)
-        for (int dx = -R; dx <= R; ++dx) {
-          const double w = r - sqrt((double)(dx * dx + dy * dy + dz * dz));
-          const int ii = i + dx, jj = j + dy, kk = k + dz;
-          if (w <= 0 || ii < 0 || ii >= nx || jj < 0 || jj >= ny || kk < 0 || kk >= nz) continue;
-          const long long q = ii + (long long)nx * (jj + (long long)ny * kk);
-          double s, W;
-          hat_sums(ii, jj, kk, nx, ny, nz, R, r, nullptr, s, W);
-          acc += w * (b ? a[q] * b[q] : a[q]) / W;
-        }
-    y[e] = acc;
-  }
-}
-
-// x_new = clip(x sqrt(max(0, -dc) / (lam dv)), max(0, x - move), min(1, x + move))
-__global__ __launch_bounds__(TO_BLOCK) void k_oc(const double* __restrict__ x, const double* __restrict__ dc,
-                                                 const double* __restrict__ dv, long long n, double lam,
-                                                 double move, double* __restrict__ xn) {
-  for (long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x; e < n; e += (long long)gridDim.x * TO_BLOCK) {
-    const double ratio = fmax(0.0, -dc[e]) / fmax(dv[e], 1e-300);
-    const double v = x[e] * sqrt(ratio / lam);
-    xn[e] = fmin(fmin(1.0, x[e] + move), fmax(fmax(0.0, x[e] - move), v));
-  }
-}
-
-// Per-block partials of sum_e project(H x)_e (mode 0) or max_e |a_e - b_e|
-// (mode 1), fixed order.
-__global__ __launch_bounds__(TO_BLOCK) void k_to_reduce(const double* __restrict__ x, const double* __restrict__ b,
-                                                        int nx, int ny, int nz, int R, double r, double beta,
-                                                        double eta, int mode, double* __restrict__ part) {
-  __shared__ double red[TO_BLOCK / 64];
-  const long long n = (long long)nx * ny * nz;
-  double acc = 0.0;
-  const double den = tanh(beta * eta) + tanh(beta * (1.0 - eta));
-  for (long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x; e < n; e += (long long)gridDim.x * TO_BLOCK) {
-    if (mode == 0) {
-      int i, j, k;
-      elem_ijk(e, nx, ny, i, j, k);
-      double s, W;
-      hat_sums(i, j, k, nx, ny, nz, R, r, x, s, W);
-      acc += (tanh(beta * eta) + tanh(beta * (s / W - eta))) / den;
-    } else {
-      acc = fmax(acc, fabs(x[e] - b[e]));
-    }
-  }
+// W_e: the weights of the in-grid offsets of element (i, j, k), in order
+template <int R>
+__device__ __forceinline__ double weight_sum(const Hat& h, const Dims& D, int i, int j, int k) {
+  if (i >= R && i < D.nx - R && j >= R && j < D.ny - R && k >= R && k < D.nz - R) return h.wsum;
+  double W = 0.0;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const double o = __shfl_xor(acc, off, 64);
-    acc = mode == 0 ? acc + o : fmax(acc, o);
+  for (int dz = -R; dz <= R; ++dz) {
+    if (k + dz < 0 || k + dz >= D.nz) continue;
+#pragma unroll
+    for (int dy = -R; dy <= R; ++dy) {
+      if (j + dy < 0 || j + dy >= D.ny) continue;
+#pragma unroll
+      for (int dx = -R; dx <= R; ++dx)
+        W += i + dx >= 0 && i + dx < D.nx ? h.w[dx * dx + dy * dy + dz * dz] : 0.0;
+    }
   }
+  return W;
+}
+
+// v(e, i, j, k) of every element of tile t and its halo into sv (0 outside the grid)
+template <int R, class F>
+__device__ __forceinline__ void stage_tile(const Dims& D, int t, double* sv, F&& v) {
+  using T = Tile<R>;
+  const int tk = t / (D.tx * D.ty), r = t - tk * D.tx * D.ty, tj = r / D.tx, ti = r - tj * D.tx;
+  for (int q = threadIdx.x; q < T::N; q += TO_BLOCK) {
+    const int sk = q / (T::SX * T::SY), sr = q - sk * T::SX * T::SY, sj = sr / T::SX, si = sr - sj * T::SX;
+    const int i = ti * T::X + si - R, j = tj * T::Y + sj - R, k = tk * T::Z + sk - R;
+    const bool in = i >= 0 && i < D.nx && j >= 0 && j < D.ny && k >= 0 && k < D.nz;
+    sv[q] = in ? v(i + (long long)D.nx * (j + (long long)D.ny * k), i, j, k) : 0.0;
+  }
+}
+// this thread's element of tile t and its place in the staged tile
+template <int R>
+__device__ __forceinline__ bool tile_elem(const Dims& D, int t, int& i, int& j, int& k, int& at) {
+  using T = Tile<R>;
+  const int tk = t / (D.tx * D.ty), r = t - tk * D.tx * D.ty, tj = r / D.tx, ti = r - tj * D.tx;
+  const int x = threadIdx.x & 15, y = (threadIdx.x >> 4) & 3, z = threadIdx.x >> 6;
+  i = ti * T::X + x;
+  j = tj * T::Y + y;
+  k = tk * T::Z + z;
+  at = ((z + R) * T::SY + y + R) * T::SX + x + R;
+  return i < D.nx && j < D.ny && k < D.nz;
+}
+// sum of w v over the offsets with w > 0, in order (the halo outside the grid
+// holds 0)
+template <int R>
+__device__ __forceinline__ double hat_sum(const Hat& h, const double* sv, int at) {
+  using T = Tile<R>;
+  double s = 0.0;
+#pragma unroll
+  for (int dz = -R; dz <= R; ++dz)
+#pragma unroll
+    for (int dy = -R; dy <= R; ++dy)
+#pragma unroll
+      for (int dx = -R; dx <= R; ++dx) {
+        const double w = h.w[dx * dx + dy * dy + dz * dz];
+        const double v = sv[at + (dz * T::SY + dy) * T::SX + dx];
+        s += w > 0.0 ? w * v : 0.0;
+      }
+  return s;
+}
+
+// xt = H x (and, if xbar, xbar = project(xt), dxbar its derivative); t1 =
+// tanh(beta eta), den = t1 + tanh(beta (1 - eta)).  Bound by the stencil's
+// LDS reads and the tanh; with the neighbours read from global memory and
+// their weights recomputed (a square root each) it took 11 us at 64x32x32 and
+// r_min = 1.5, 5.6 us so.
+template <int R>
+__global__ __launch_bounds__(TO_BLOCK) void k_filter(Hat h, Dims D, const double* __restrict__ x, double beta,
+                                                     double eta, double t1, double den, double* __restrict__ xt,
+                                                     double* __restrict__ xbar, double* __restrict__ dxbar) {
+  __shared__ double sv[Tile<R>::N];
+  const int t = blockIdx.x;
+  stage_tile<R>(D, t, sv, [&](long long e, int, int, int) { return x[e]; });
+  __syncthreads();
+  int i, j, k, at;
+  if (!tile_elem<R>(D, t, i, j, k, at)) return;
+  const long long e = i + (long long)D.nx * (j + (long long)D.ny * k);
+  const double v = hat_sum<R>(h, sv, at) / weight_sum<R>(h, D, i, j, k);
+  if (xt) xt[e] = v;
+  if (xbar) {
+    const double th = tanh(beta * (v - eta));
+    xbar[e] = fmin(1.0, fmax(0.0, (t1 + th) / den));   // rounding stays in [0, 1]
+    if (dxbar) dxbar[e] = beta * (1.0 - th * th) / den;
+  }
+}
+
+// y_j = sum_e w_ej a_e b_e / W_e (b may be NULL: 1).  The quotients are formed
+// once per element while the tile is staged (the stencil is symmetric, so e
+// runs over j's own stencil).  Recomputing W_e for every pair took 70 us at
+// 64x32x32 and r_min = 1.5; this form takes 5.2 us.
+template <int R>
+__global__ __launch_bounds__(TO_BLOCK) void k_filter_adj(Hat h, Dims D, const double* __restrict__ a,
+                                                         const double* __restrict__ b, double* __restrict__ y) {
+  __shared__ double sv[Tile<R>::N];
+  const int t = blockIdx.x;
+  stage_tile<R>(D, t, sv, [&](long long e, int i, int j, int k) {
+    return (b ? a[e] * b[e] : a[e]) / weight_sum<R>(h, D, i, j, k);
+  });
+  __syncthreads();
+  int i, j, k, at;
+  if (tile_elem<R>(D, t, i, j, k, at)) y[i + (long long)D.nx * (j + (long long)D.ny * k)] = hat_sum<R>(h, sv, at);
+}
+
+__device__ __forceinline__ double block_sum(double v, double* sh) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+// the workgroup's part of sum_e tanh(beta ((H v)_e - eta)) over tiles b, b + nb, ...
+template <int R, class F>
+__device__ __forceinline__ double volume_part(const Hat& h, const Dims& D, int b, int nb, double beta, double eta,
+                                              double* sv, double* sh, F&& v) {
+  double acc = 0.0;
+  const int nt = D.tx * D.ty * D.tz;
+  for (int t = b; t < nt; t += nb) {
+    __syncthreads();              // the previous tile's reads
+    stage_tile<R>(D, t, sv, v);
+    __syncthreads();
+    int i, j, k, at;
+    if (tile_elem<R>(D, t, i, j, k, at))
+      acc += tanh(beta * (hat_sum<R>(h, sv, at) / weight_sum<R>(h, D, i, j, k) - eta));
+  }
+  __syncthreads();
+  return block_sum(acc, sh);
+}
+
+template <int R>
+__global__ __launch_bounds__(TO_BLOCK) void k_volume(Hat h, Dims D, const double* __restrict__ x, double beta,
+                                                     double eta, double* __restrict__ part) {
+  __shared__ double sv[Tile<R>::N], sh[4];
+  const double s = volume_part<R>(h, D, blockIdx.x, gridDim.x, beta, eta, sv, sh,
+                                  [&](long long e, int, int, int) { return x[e]; });
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+// per-block maxima of |a - b|
+__global__ __launch_bounds__(TO_BLOCK) void k_max_change(const double* __restrict__ a, const double* __restrict__ b,
+                                                         long long n, double* __restrict__ part) {
+  __shared__ double red[TO_BLOCK / 64];
+  double acc = 0.0;
+  for (long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x; e < n; e += (long long)gridDim.x * TO_BLOCK)
+    acc = fmax(acc, fabs(a[e] - b[e]));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc = fmax(acc, __shfl_xor(acc, off, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = red[0];
-    for (int w = 1; w < TO_BLOCK / 64; ++w) s = mode == 0 ? s + red[w] : fmax(s, red[w]);
-    part[blockIdx.x] = s;
+  if (threadIdx.x == 0) part[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
+// ---- the OC step.  The bisection of the multiplier from [0, 1e9] takes about
+// 70 halvings, each needing the volume of the design at its midpoint.  A
+// launch evaluates several midpoints at once, one set of workgroups per
+// midpoint, and the next launch (every workgroup for itself, from the
+// partial sums) takes the decisions, so nothing returns to the host on the
+// way.  With a bracket [l1, l2], l1 > 0, the midpoints are those of the next
+// `depth` levels of the bisection (2^depth - 1 of them).  While l1 = 0 the
+// midpoints are l2 / 2, l2 / 4, ...: the volume does not increase with the
+// multiplier, so one that is not above the target decides every larger one,
+// and the midpoints are taken `stride` halvings apart until one is above.
+// The halvings, their order, the stop test and the midpoints are those of
+// one evaluation at a time; 64x32x32 took 31 us per halving with the volume
+// read back after each, 2.0 ms in all, now 0.2 ms.
+constexpr int OC_MAX_CAND = 7;    // depth 3
+constexpr int OC_STRIDE = 6;
+constexpr int OC_MAX_HALVINGS = 200;
+struct OcState {
+  double l1, l2, lm;
+  double it, done, stride;        // halvings taken; stop test met; left-phase stride
+};
+constexpr int OC_STATE_W = 8;
+static_assert(sizeof(OcState) <= OC_STATE_W * sizeof(double), "state words");
+
+__device__ __forceinline__ bool oc_more(const OcState& s) {
+  return s.it < OC_MAX_HALVINGS && (s.l2 - s.l1) / (s.l1 + s.l2) > 1e-9;
+}
+// the c-th midpoint (c < nc) the launch after state s evaluates; 0: none
+__device__ __forceinline__ double oc_midpoint(const OcState& s, int c) {
+  if (s.l1 == 0.0) {
+    const double lev = s.stride * (c + 1);
+    return s.it + lev <= OC_MAX_HALVINGS ? ldexp(s.l2, -(int)lev) : 0.0;
   }
+  // node c + 1 of the heap-ordered tree of halvings: its path from the top bit
+  double l1 = s.l1, l2 = s.l2;
+  for (int b = 30 - __clz(c + 1); b >= 0; --b) {
+    const double m = 0.5 * (l1 + l2);
+    if ((c + 1) >> b & 1) l1 = m;
+    else l2 = m;
+  }
+  return 0.5 * (l1 + l2);
+}
+// the state after the volumes of those midpoints
+__device__ __forceinline__ OcState oc_advance(OcState s, const double* vol, int nc, double target) {
+  if (s.l1 == 0.0) {
+    const int stride = (int)s.stride;
+    for (int c = 0; c < nc; ++c) {
+      if (s.it + stride > OC_MAX_HALVINGS) {
+        // the last halvings before the cap one by one
+        if (stride == 1) break;
+        s.stride = 1.0;
+        break;
+      }
+      if (vol[c] > target) {
+        if (stride == 1) {
+          s.l1 = s.lm = 0.5 * s.l2;
+          s.it += 1.0;
+        } else {
+          s.stride = 1.0;         // within the next `stride` halvings
+        }
+        break;
+      }
+      s.l2 = s.lm = ldexp(s.l2, -stride);
+      s.it += stride;
+    }
+  } else {
+    for (int c = 0; c < nc && oc_more(s);) {
+      s.lm = 0.5 * (s.l1 + s.l2);
+      s.it += 1.0;
+      const bool above = vol[c] > target;
+      if (above) s.l1 = s.lm;
+      else s.l2 = s.lm;
+      c = 2 * c + 1 + (above ? 1 : 0);
+    }
+  }
+  if (!oc_more(s)) s.done = 1.0;
+  return s;
+}
+
+// the state this launch starts from: the previous launch's state advanced by
+// its partial sums (prev NULL: the first launch), the same in every workgroup
+__device__ __forceinline__ OcState oc_state(const double* prev, int nb, int nc, double target, double* vol) {
+  if (!prev) return {0.0, 1e9, 0.5e9, 0.0, 0.0, (double)OC_STRIDE};
+  OcState s = *(const OcState*)prev;
+  if (s.done != 0.0) return s;
+  const int c = threadIdx.x >> 5, l = threadIdx.x & 31;
+  double a = 0.0;
+  if (c < nc)
+    for (int b = l; b < nb; b += 32) a += prev[OC_STATE_W + c * nb + b];
+#pragma unroll
+  for (int off = 16; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+  if (l == 0) vol[c] = a;
+  __syncthreads();
+  return oc_advance(s, vol, nc, target);
+}
+
+// v within the move limit and [0, 1]
+__device__ __forceinline__ double oc_clip(double x, double v, double move) {
+  return fmin(fmin(1.0, x + move), fmax(fmax(0.0, x - move), v));
+}
+
+__device__ __forceinline__ double oc_ratio(double dc, double dv) { return fmax(0.0, -dc) / fmax(dv, 1e-300); }
+
+// xs = x sqrt(max(0, -dc) / dv): the unclipped design at multiplier 1
+__global__ __launch_bounds__(TO_BLOCK) void k_oc_unit(const double* __restrict__ x, const double* __restrict__ dc,
+                                                      const double* __restrict__ dv, long long n,
+                                                      double* __restrict__ xs) {
+  const long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x;
+  if (e < n) xs[e] = x[e] * sqrt(oc_ratio(dc[e], dv[e]));
+}
+
+// grid (nb, nc): partial volumes of midpoint blockIdx.y into next (of the
+// designs xs / sqrt(lam), one multiplication per element)
+template <int R>
+__global__ __launch_bounds__(TO_BLOCK) void k_oc_volumes(Hat h, Dims D, const double* __restrict__ x,
+                                                         const double* __restrict__ xs, double move, double beta,
+                                                         double eta, double target,
+                                                         const double* __restrict__ prev, double* __restrict__ next) {
+  __shared__ double sv[Tile<R>::N], sh[4], vol[TO_BLOCK / 32];
+  const int nb = gridDim.x, nc = gridDim.y, c = blockIdx.y;
+  const OcState s = oc_state(prev, nb, nc, target, vol);
+  if (blockIdx.x == 0 && c == 0 && threadIdx.x == 0) *(OcState*)next = s;
+  if (s.done != 0.0) return;
+  const double lam = oc_midpoint(s, c);
+  if (lam == 0.0) {
+    if (threadIdx.x == 0) next[OC_STATE_W + c * nb + blockIdx.x] = 0.0;
+    return;
+  }
+  const double il = 1.0 / sqrt(lam);
+  const double a = volume_part<R>(h, D, blockIdx.x, nb, beta, eta, sv, sh, [&](long long e, int, int, int) {
+    return oc_clip(x[e], xs[e] * il, move);
+  });
+  if (threadIdx.x == 0) next[OC_STATE_W + c * nb + blockIdx.x] = a;
+}
+
+// once the stop test is met: the design of the last midpoint,
+// x sqrt(ratio / lam), over the unit designs
+__global__ __launch_bounds__(TO_BLOCK) void k_oc_design(const double* __restrict__ x, const double* __restrict__ dc,
+                                                        const double* __restrict__ dv, long long n, double move,
+                                                        double target, int nb, int nc, const double* prev,
+                                                        double* state, double* __restrict__ xn) {
+  __shared__ double vol[TO_BLOCK / 32];
+  const OcState s = oc_state(prev, nb, nc, target, vol);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *(OcState*)state = s;
+  const long long e = (long long)blockIdx.x * TO_BLOCK + threadIdx.x;
+  if (s.done != 0.0 && e < n) xn[e] = oc_clip(x[e], x[e] * sqrt(oc_ratio(dc[e], dv[e]) / s.lm), move);
 }
 
 int stencil_R(double r_min) { return (int)std::floor(r_min); }
 
 int nblocks(long long n) { return (int)std::max<long long>(1, std::min<long long>(1024, (n + TO_BLOCK - 1) / TO_BLOCK)); }
+unsigned nblocks_all(long long n) { return (unsigned)((n + TO_BLOCK - 1) / TO_BLOCK); }
 
 long long n_elem(const tg_grid* g) { return (long long)g->nx * g->ny * g->nz; }
 
@@ -158,43 +366,130 @@ int check_r(double r_min) {
   return TG_OK;
 }
 
-// sum (mode 0) or max (mode 1) through the grid's partial-sum scratch
-int reduce_host(const tg_grid* g, const double* x, const double* b, double r, double beta, double eta, int mode,
-                hipStream_t s, double* out) {
-  const long long n = n_elem(g);
-  const int nb = nblocks(n);
-  if ((long long)nb > (long long)TG_PART_W * g->lv[0].n_chunks) return fail(TG_EINVAL, "partial buffer too small");
-  if (mode == 1 && !b) return fail(TG_EINVAL, "max-change reduction needs two vectors");
-  k_to_reduce<<<nb, TO_BLOCK, 0, s>>>(x, b, g->nx, g->ny, g->nz, stencil_R(r), r, beta, eta, mode, g->desc.part);
-  TG_HIP(hipGetLastError());
-  std::vector<double> h(nb);
+Hat hat_of(double r) {
+  Hat h = {};
+  const int R = stencil_R(r);
+  for (int q = 0; q <= 3 * R * R; ++q) h.w[q] = std::max(0.0, r - std::sqrt((double)q));
+  for (int dz = -R; dz <= R; ++dz)
+    for (int dy = -R; dy <= R; ++dy)
+      for (int dx = -R; dx <= R; ++dx) h.wsum += h.w[dx * dx + dy * dy + dz * dz];
+  return h;
+}
+
+Dims dims_of(const tg_grid* g) {
+  using T = Tile<0>;
+  return {g->nx, g->ny, g->nz, (g->nx + T::X - 1) / T::X, (g->ny + T::Y - 1) / T::Y, (g->nz + T::Z - 1) / T::Z,
+          n_elem(g)};
+}
+unsigned n_tiles(const Dims& D) { return (unsigned)D.tx * D.ty * D.tz; }
+
+struct Projection {
+  double beta, eta, t1, den;
+};
+Projection projection_of(double beta, double eta) {
+  const double t1 = std::tanh(beta * eta);
+  return {beta, eta, t1, t1 + std::tanh(beta * (1.0 - eta))};
+}
+
+// LAUNCH(R) with the stencil half-width as a constant
+#define TO_BY_R(r, LAUNCH)      \
+  do {                          \
+    switch (stencil_R(r)) {     \
+      case 0: LAUNCH(0); break; \
+      case 1: LAUNCH(1); break; \
+      case 2: LAUNCH(2); break; \
+      default: LAUNCH(3);       \
+    }                           \
+    TG_HIP(hipGetLastError());  \
+  } while (0)
+
+int launch_filter(const tg_grid* g, const double* x, double r, const Projection& pr, double* xt, double* xbar,
+                  double* dxbar, hipStream_t s) {
+  const Hat h = hat_of(r);
+  const Dims D = dims_of(g);
+#define TO_FILTER(R) k_filter<R><<<n_tiles(D), TO_BLOCK, 0, s>>>(h, D, x, pr.beta, pr.eta, pr.t1, pr.den, xt, xbar, dxbar)
+  TO_BY_R(r, TO_FILTER);
+#undef TO_FILTER
+  return TG_OK;
+}
+
+int read_parts(const tg_grid* g, int nb, std::vector<double>& h, hipStream_t s) {
+  h.resize(nb);
   TG_HIP(hipMemcpyAsync(h.data(), g->desc.part, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
   TG_HIP(hipStreamSynchronize(s));
-  double acc = h[0];
-  for (int i = 1; i < nb; ++i) acc = mode == 0 ? acc + h[i] : std::max(acc, h[i]);
-  *out = acc;
+  return TG_OK;
+}
+
+// sum_e project(H x)_e through the grid's partial-sum scratch
+int volume_host(const tg_grid* g, const double* x, double r, const Projection& pr, hipStream_t s, double* out) {
+  const Hat h = hat_of(r);
+  const Dims D = dims_of(g);
+  const int nb = (int)std::min<long long>(n_tiles(D), std::min<long long>(256, (long long)TG_PART_W * g->lv[0].n_chunks));
+#define TO_VOLUME(R) k_volume<R><<<nb, TO_BLOCK, 0, s>>>(h, D, x, pr.beta, pr.eta, g->desc.part)
+  TO_BY_R(r, TO_VOLUME);
+#undef TO_VOLUME
+  std::vector<double> p;
+  const int rc = read_parts(g, nb, p, s);
+  if (rc) return rc;
+  double th = 0.0;
+  for (double v : p) th += v;
+  *out = ((double)D.n * pr.t1 + th) / pr.den;
+  return TG_OK;
+}
+
+// max_e |a_e - b_e|
+int change_host(const tg_grid* g, const double* a, const double* b, hipStream_t s, double* out) {
+  const long long n = n_elem(g);
+  const int nb = (int)std::min<long long>(nblocks(n), (long long)TG_PART_W * g->lv[0].n_chunks);
+  k_max_change<<<nb, TO_BLOCK, 0, s>>>(a, b, n, g->desc.part);
+  TG_HIP(hipGetLastError());
+  std::vector<double> p;
+  const int rc = read_parts(g, nb, p, s);
+  if (rc) return rc;
+  *out = *std::max_element(p.begin(), p.end());
   return TG_OK;
 }
 
 int oc_update(const tg_grid* g, const double* x, const double* dc, const double* dv, double volfrac, double move,
-              double r, double beta, double eta, double* xn, double* lam_out, hipStream_t s) {
-  const long long n = n_elem(g);
-  const double target = volfrac * (double)n;
-  double l1 = 0.0, l2 = 1e9, lm = 0.5e9;
-  for (int it = 0; it < 200 && (l2 - l1) / (l1 + l2) > 1e-9; ++it) {
-    lm = 0.5 * (l1 + l2);
-    k_oc<<<nblocks(n), TO_BLOCK, 0, s>>>(x, dc, dv, n, lm, move, xn);
+              double r, const Projection& pr, double* xn, double* lam_out, hipStream_t s) {
+  const Hat h = hat_of(r);
+  const Dims D = dims_of(g);
+  // the volume sum_e (t1 + tanh(...)_e) / den against volfrac n, as a bound on the sum of the tanh
+  const double target = volfrac * (double)D.n * pr.den - (double)D.n * pr.t1;
+  // Midpoints per launch: a launch costs about 7 us beside its work (its own
+  // start and the previous launch's sums), and the work of one midpoint is
+  // about 1 us per 65,536 elements (14 us per launch of seven there), so three
+  // levels at once pay up to 2^18 elements and two up to 2^20.
+  const int nc = D.n <= (1 << 18) ? 7 : D.n <= (1 << 20) ? 3 : 1;
+  // two buffers of one state and nc rows of partial sums each, and a state
+  const long long cap = (long long)TG_PART_W * g->lv[0].n_chunks;
+  const int nb = (int)std::min<long long>({(long long)n_tiles(D), 128, (cap - 3 * OC_STATE_W) / (2 * nc)});
+  double* buf[2] = {g->desc.part, g->desc.part + OC_STATE_W + (long long)nc * nb};
+  double* fin = buf[1] + OC_STATE_W + (long long)nc * nb;
+  k_oc_unit<<<nblocks_all(D.n), TO_BLOCK, 0, s>>>(x, dc, dv, D.n, xn);
+  TG_HIP(hipGetLastError());
+  const double* prev = nullptr;
+  int t = 0;
+  // 72 halvings' launches before the first look at the state, then some more
+  for (int more = nc == 7 ? 14 : nc == 3 ? 24 : 48;; more = 4) {
+    for (int q = 0; q < more; ++q, ++t) {
+      double* next = buf[t & 1];
+#define TO_OC(R)                                                                                                    \
+  k_oc_volumes<R><<<dim3(nb, nc), TO_BLOCK, 0, s>>>(h, D, x, xn, move, pr.beta, pr.eta, target, prev, next)
+      TO_BY_R(r, TO_OC);
+#undef TO_OC
+      prev = next;
+    }
+    k_oc_design<<<nblocks_all(D.n), TO_BLOCK, 0, s>>>(x, dc, dv, D.n, move, target, nb, nc, prev, fin, xn);
     TG_HIP(hipGetLastError());
-    double vol = 0.0;
-    const int rc = reduce_host(g, xn, nullptr, r, beta, eta, 0, s, &vol);
-    if (rc) return rc;
-    if (vol > target)
-      l1 = lm;
-    else
-      l2 = lm;
+    OcState st;
+    TG_HIP(hipMemcpyAsync(&st, fin, sizeof(st), hipMemcpyDeviceToHost, s));
+    TG_HIP(hipStreamSynchronize(s));
+    if (st.done != 0.0) {
+      if (lam_out) *lam_out = st.lm;
+      return TG_OK;
+    }
   }
-  if (lam_out) *lam_out = lm;
-  return TG_OK;
 }
 
 }  // namespace
@@ -209,11 +504,7 @@ int tg_density_filter(const tg_grid* g, const double* x_d, double r_min, double*
   if (rc) return rc;
   if ((rc = check_r(r_min))) return rc;
   if (!x_d || !xt_d) return fail(TG_EINVAL, "NULL argument");
-  hipStream_t s = (hipStream_t)stream;
-  k_filter<<<nblocks(n_elem(g)), TO_BLOCK, 0, s>>>(x_d, g->nx, g->ny, g->nz, stencil_R(r_min), r_min, 0.0, 0.5,
-                                                     xt_d, nullptr, nullptr);
-  TG_HIP(hipGetLastError());
-  return TG_OK;
+  return launch_filter(g, x_d, r_min, {0.0, 0.5, 0.0, 1.0}, xt_d, nullptr, nullptr, (hipStream_t)stream);
 }
 
 int tg_density_filter_adjoint(const tg_grid* g, const double* a_d, const double* b_d, double r_min, double* y_d,
@@ -224,8 +515,11 @@ int tg_density_filter_adjoint(const tg_grid* g, const double* a_d, const double*
   if (!a_d || !y_d) return fail(TG_EINVAL, "NULL argument");
   if (a_d == y_d || b_d == y_d) return fail(TG_EINVAL, "output must not alias an input");
   hipStream_t s = (hipStream_t)stream;
-  k_filter_adj<<<nblocks(n_elem(g)), TO_BLOCK, 0, s>>>(a_d, b_d, g->nx, g->ny, g->nz, stencil_R(r_min), r_min, y_d);
-  TG_HIP(hipGetLastError());
+  const Hat h = hat_of(r_min);
+  const Dims D = dims_of(g);
+#define TO_ADJ(R) k_filter_adj<R><<<n_tiles(D), TO_BLOCK, 0, s>>>(h, D, a_d, b_d, y_d)
+  TO_BY_R(r_min, TO_ADJ);
+#undef TO_ADJ
   return TG_OK;
 }
 
@@ -236,11 +530,7 @@ int tg_filter_project(const tg_grid* g, const double* x_d, double r_min, double 
   if ((rc = check_r(r_min))) return rc;
   if (!x_d || !xbar_d) return fail(TG_EINVAL, "NULL argument");
   if (!(beta > 0) || !(eta > 0 && eta < 1)) return fail(TG_EINVAL, "need beta > 0 and 0 < eta < 1");
-  hipStream_t s = (hipStream_t)stream;
-  k_filter<<<nblocks(n_elem(g)), TO_BLOCK, 0, s>>>(x_d, g->nx, g->ny, g->nz, stencil_R(r_min), r_min, beta, eta,
-                                                     xt_d, xbar_d, dxbar_d);
-  TG_HIP(hipGetLastError());
-  return TG_OK;
+  return launch_filter(g, x_d, r_min, projection_of(beta, eta), xt_d, xbar_d, dxbar_d, (hipStream_t)stream);
 }
 
 int tg_oc_update(const tg_grid* g, const double* x_d, const double* dc_d, const double* dv_d, double volfrac,
@@ -252,7 +542,8 @@ int tg_oc_update(const tg_grid* g, const double* x_d, const double* dc_d, const 
   if (!x_d || !dc_d || !dv_d || !x_new_d) return fail(TG_EINVAL, "NULL argument");
   if (!(volfrac > 0 && volfrac < 1) || !(move > 0) || !(beta > 0) || !(eta > 0 && eta < 1))
     return fail(TG_EINVAL, "need 0 < volfrac < 1, move > 0, beta > 0, 0 < eta < 1");
-  return oc_update(g, x_d, dc_d, dv_d, volfrac, move, r_min, beta, eta, x_new_d, lambda_h, (hipStream_t)stream);
+  return oc_update(g, x_d, dc_d, dv_d, volfrac, move, r_min, projection_of(beta, eta), x_new_d, lambda_h,
+                   (hipStream_t)stream);
 }
 
 void tg_default_topopt(tg_topopt_opts* o) {
@@ -373,13 +664,13 @@ int tg_topopt_run(tg_grid* g, const double* f_d, const tg_topopt_opts* o, void* 
     if ((rc = tg_compliance_sensitivity(g, xbar, p, floor, f_d, u, nullptr, dcp, &R.compliance, stream))) return rc;
     if ((rc = tg_density_filter_adjoint(g, dcp, dxbar, r, dcd, stream))) return rc;
     if ((rc = tg_density_filter_adjoint(g, dxbar, nullptr, r, dv, stream))) return rc;
-    if ((rc = oc_update(g, x_d, dcd, dv, o->volfrac, move, r, beta, eta, xn, nullptr, s))) return rc;
+    if ((rc = oc_update(g, x_d, dcd, dv, o->volfrac, move, r, projection_of(beta, eta), xn, nullptr, s))) return rc;
     double vol = 0.0;
     // volume of the physical density this iteration solved with, and the
     // largest design change of the step
-    if ((rc = reduce_host(g, x_d, nullptr, r, beta, eta, 0, s, &vol))) return rc;
+    if ((rc = volume_host(g, x_d, r, projection_of(beta, eta), s, &vol))) return rc;
     R.volume = vol / (double)ne;
-    if ((rc = reduce_host(g, xn, x_d, r, beta, eta, 1, s, &R.change))) return rc;
+    if ((rc = change_host(g, xn, x_d, s, &R.change))) return rc;
     TG_HIP(hipMemcpyAsync(x_d, xn, ne * sizeof(double), hipMemcpyDeviceToDevice, s));
     TG_HIP(hipStreamSynchronize(s));
     R.ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
