@@ -13,6 +13,8 @@
 // four in-plane element contributions: a complete, atomic-free, deterministic
 // K u at node layer k, fused with the residual or the damped node-block Jacobi
 // update.  Output nodes: 15 x 15 columns per workgroup, ZC node layers.
+#include <algorithm>
+#include <climits>
 #include <cmath>
 #include <mutex>
 #include <cstring>
@@ -957,25 +959,38 @@ int rz_tiles(const tg_grid* g, int l, int zmax) {
   return ((NXc + RZ_C - 1) / RZ_C) * ((NYc + RZ_C - 1) / RZ_C) * ((NZc + m - 1) / m);
 }
 
-// Per level, the tallest z-tile in {16, 12, 8, 6, 4} that gives >= 2048
-// workgroups over the whole batch, else 4.  Every tile recomputes one element
-// layer, so taller tiles do less redundant work; shorter tiles give more
-// parallelism.
-void batch_choose_zc(Batch* b) {
-  const int cand[5] = {16, 12, 8, 6, 4};
-  for (int l = 0; l < TG_MAXLEV; ++l) {
-    int pick = 4;
-    for (int c : cand) {
-      long long tiles = 0;
-      for (auto* g : b->grids)
-        if (l < g->nlev) tiles += zm_tiles(g, l, c);
-      if (tiles >= 2048) {
-        pick = c;
-        break;
-      }
+// z-tile height of level l for the problems `which` of the batch.  Every tile
+// recomputes one element layer, so taller tiles do less redundant work, but a
+// tile marches its layers one after the other (about 1 us each while the
+// device is not full).  Up to 768 tiles (three per CU) the march is what
+// counts: the lowest height that does not exceed that, at most 6.  Beyond, the
+// tallest of 16, 12 and 8 that still gives 2048 tiles, and 24 on grids of at
+// least 64 node layers from 768 tiles on.  Measured V-cycles, at heights of at
+// least 4 before and so now: 69 -> 59 us (16x8x8 FP64), 159 -> 129 (64x32x32
+// split BF16), 417 -> 300 (128x64x64 FP64); a 256x128x128 sweep 84 -> 68 us
+// from 8 layers to 22.
+int zm_rule(const Batch* b, const std::vector<int>& which, int l) {
+  int nz_min = INT_MAX;
+  auto tiles = [&](int c) {
+    long long t = 0;
+    for (int p : which) {
+      const tg_grid* g = b->grids[p];
+      if (l < g->nlev) t += zm_tiles(g, l, c);
     }
-    b->zc[l] = pick;
-  }
+    return t;
+  };
+  for (int p : which)
+    if (l < b->grids[p]->nlev) nz_min = std::min(nz_min, b->grids[p]->lv[l].ez + 1);
+  if (nz_min >= 64 && nz_min < INT_MAX && tiles(24) >= 768) return 24;
+  for (int c : {16, 12, 8})
+    if (tiles(c) >= 2048) return c;
+  return (int)std::min<long long>(6, std::max<long long>(1, (tiles(1) + 767) / 768));
+}
+
+void batch_choose_zc(Batch* b) {
+  std::vector<int> all(b->n);
+  for (int i = 0; i < b->n; ++i) all[i] = i;
+  for (int l = 0; l < TG_MAXLEV; ++l) b->zc[l] = zm_rule(b, all, l);
 }
 
 template <class T> static ModeCoef<T> mcoef(const tg_grid* g);

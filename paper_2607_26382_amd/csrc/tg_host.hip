@@ -297,34 +297,11 @@ int batch_upload_desc(Batch* b, hipStream_t s) {
   return TG_OK;
 }
 
-// z-tile caps for a subset of the batch: while few problems run (the tail of a
-// ladder), a level whose z-march launch would have fewer than 1024
-// workgroups at the chosen heights gets the tallest height in {16, 12, 8, 6,
-// 4, 3} that restores 1024, else 2.  Shorter tiles redo one element layer
-// more often but shorten each workgroup's serial march, and the device is
-// mostly idle then.  Results do not depend on the heights.
+// z-tile caps for a subset of the batch (the tail of a ladder): the height the
+// rule gives the problems that run, which is lower where fewer of them do.
+// Results do not depend on the heights.
 static void batch_tile_caps(const Batch* b, const std::vector<int>& active, int* cap) {
-  for (int l = 0; l < TG_MAXLEV; ++l) cap[l] = 1 << 30;
-  if ((int)active.size() >= b->n) return;
-  for (int l = 0; l < TG_MAXLEV; ++l) {
-    auto tiles = [&](int c) {
-      long long t = 0;
-      for (int p : active) {
-        const tg_grid* g = b->grids[p];
-        if (l < g->nlev - 1) t += zm_tiles(g, l, std::min(batch_zc(b, p, l), c));
-      }
-      return t;
-    };
-    const long long t0 = tiles(1 << 30);
-    if (t0 == 0 || t0 >= 1024) continue;
-    int pick = 2;
-    for (int c : {16, 12, 8, 6, 4, 3})
-      if (tiles(c) >= 1024) {
-        pick = c;
-        break;
-      }
-    cap[l] = pick;
-  }
+  for (int l = 0; l < TG_MAXLEV; ++l) cap[l] = (int)active.size() >= b->n ? 1 << 30 : zm_rule(b, active, l);
 }
 
 int batch_set_active(Batch* b, const std::vector<int>& active, hipStream_t s, bool with_elem) {

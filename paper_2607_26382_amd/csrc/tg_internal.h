@@ -331,6 +331,7 @@ int galerkin1_values(const double* Ke, double* out);
 int zm_height(int NZ, int zmax);
 int zm_tiles(const tg_grid* g, int l, int zmax);
 int rz_tiles(const tg_grid* g, int l, int zmax);
+int zm_rule(const Batch* b, const std::vector<int>& which, int l);
 void batch_choose_zc(Batch* b);
 template <class T>
 // op 3 (residual fused with the restriction): sy is the next level's
