@@ -33,12 +33,13 @@ namespace tg {
 __host__ __device__ __forceinline__ float mad_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __host__ __device__ __forceinline__ double mad_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-enum { FOP_APPLY = 0, FOP_RESID = 1, FOP_SMOOTH = 2, FOP_RESTRICT = 3, FOP_SMOOTH1 = 4 };
+enum { FOP_APPLY = 0, FOP_RESID = 1, FOP_SMOOTH = 2, FOP_RESTRICT = 3, FOP_SMOOTH1 = 4, FOP_SMOOTH1E = 5 };
 // FOP_SMOOTH1 (level 0): the first two sweeps from x = 0 in one pass.  The
 // right-hand side is read from an FP64 slot (sb), times the per-problem scale
 // small[sx] when sx >= 0; every staged node gets x = w D^-1 b on the fly (the
 // first sweep), the output is the second sweep x + w D^-1 (b - K x), and the
-// FP32 copy of b that later sweeps read goes to slot sy2.
+// FP32 copy of b that later sweeps read goes to slot sy2.  FOP_SMOOTH1E: the
+// same with b read from the external vector eb_ of type T, unscaled.
 
 // Tiling of the residual sweep fused with the restriction (OP = FOP_RESTRICT):
 // a tile owns 7 x 7 coarse node columns and m coarse node layers, and computes
@@ -433,15 +434,22 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
     T a0, a1, a2, e0, e1, e2;
     T b0, b1, b2;              // FOP_SMOOTH1: b at the own node
   };
-  constexpr bool S1 = (OP == FOP_SMOOTH1);
+  constexpr bool S1 = (OP == FOP_SMOOTH1 || OP == FOP_SMOOTH1E);
   const double in_scale = (S1 && sx >= 0) ? P.small[sx] : 1.0;
   // FOP_SMOOTH1: b at node (column base, layer k) from the FP64 slot, scaled,
   // and the first sweep x = w D^-1 b there
   auto first_sweep = [&](long long base, int k, T& x0, T& x1, T& x2, T& c0, T& c1, T& c2) {
-    const double TG_GLOBAL* bp = gp(P.lv[0].vec64 + (long long)sb * L.stride) + base + lstride * k;
-    c0 = T(bp[0] * in_scale);
-    c1 = T(bp[1] * in_scale);
-    c2 = T(bp[2] * in_scale);
+    if constexpr (OP == FOP_SMOOTH1E) {
+      const T TG_GLOBAL* bp = gp((const T*)eb_) + base + lstride * k;
+      c0 = bp[0];
+      c1 = bp[1];
+      c2 = bp[2];
+    } else {
+      const double TG_GLOBAL* bp = gp(P.lv[0].vec64 + (long long)sb * L.stride) + base + lstride * k;
+      c0 = T(bp[0] * in_scale);
+      c1 = T(bp[1] * in_scale);
+      c2 = T(bp[2] * in_scale);
+    }
     const T TG_GLOBAL* Dp = gp(fD<T>(L)) + 9 * (base / 3 + (lstride / 3) * k);
     x0 = omega * mad_(Dp[2], c2, mad_(Dp[1], c1, Dp[0] * c0));
     x1 = omega * mad_(Dp[5], c2, mad_(Dp[4], c1, Dp[3] * c0));
@@ -1008,26 +1016,28 @@ int launch_fine(const Batch* b, const DevList& dl, int l, int op, int sx, const 
   const ModeCoef<T> mc = mcoef<T>(b->grids[0]);
   const ProbDesc* desc = b->desc_d;
   const T om = T(omega);
-#define TG_ZM(KV)                                                                                         \
-  do {                                                                                                    \
-    if (op == FOP_APPLY)                                                                                  \
-      k_fine_zm<T, FOP_APPLY, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip);    \
-    else if (op == FOP_RESID)                                                                             \
-      k_fine_zm<T, FOP_RESID, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip);    \
-    else if (op == FOP_SMOOTH)                                                                            \
-      k_fine_zm<T, FOP_SMOOTH, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip);   \
-    else if (op == FOP_SMOOTH1)                                                                           \
-      k_fine_zm<T, FOP_SMOOTH1, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip);  \
-    else                                                                                                  \
-      k_fine_zm<T, FOP_RESTRICT, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip); \
+#define TG_ZMOP(OPV, KV) \
+  k_fine_zm<T, OPV, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip)
+#define TG_ZM(KV)                                        \
+  do {                                                   \
+    if (op == FOP_APPLY) TG_ZMOP(FOP_APPLY, KV);         \
+    else if (op == FOP_RESID) TG_ZMOP(FOP_RESID, KV);    \
+    else if (op == FOP_SMOOTH) TG_ZMOP(FOP_SMOOTH, KV);  \
+    else TG_ZMOP(FOP_RESTRICT, KV);                      \
   } while (0)
-  if (op == FOP_SMOOTH1 && l != 0) return fail(TG_EINVAL, "the fused first sweeps are a level-0 operation");
-  if (l == 0)
+  const bool first = op == FOP_SMOOTH1 || op == FOP_SMOOTH1E;
+  if (first && l != 0) return fail(TG_EINVAL, "the fused first sweeps are a level-0 operation");
+  if (op == FOP_SMOOTH1)
+    TG_ZMOP(FOP_SMOOTH1, 0);
+  else if (op == FOP_SMOOTH1E)
+    TG_ZMOP(FOP_SMOOTH1E, 0);
+  else if (l == 0)
     TG_ZM(0);
   else if (l <= TG_MF_LEVELS)
     TG_ZM(1);
   else
     TG_ZM(4);
+#undef TG_ZMOP
 #undef TG_ZM
   return TG_OK;
 }
@@ -1053,6 +1063,8 @@ int launch_fine_mfma(const Batch* b, const DevList& dl, int op, bool split, int 
     if (split) TG_MF(FOP_SMOOTH, 3, float); else TG_MF(FOP_SMOOTH, 2, float);
   } else if (op == FOP_SMOOTH1) {
     if (split) TG_MF(FOP_SMOOTH1, 3, float); else TG_MF(FOP_SMOOTH1, 2, float);
+  } else if (op == FOP_SMOOTH1E) {
+    if (split) TG_MF(FOP_SMOOTH1E, 3, float); else TG_MF(FOP_SMOOTH1E, 2, float);
   } else {
     if (split) TG_MF(FOP_RESTRICT, 3, float); else TG_MF(FOP_RESTRICT, 2, float);
   }

@@ -553,7 +553,8 @@ __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* _
 //   OP_RESTRICT: b_{l+1} = P^T (b - K x)     (residual fused with the restriction)
 //   OP_SMOOTH1: level 0, the first two sweeps from x = 0 with b read from an
 //               FP64 slot (x = scale offset, y2 = slot of b's FP32 copy)
-enum { OP_APPLY = 0, OP_RESID = 1, OP_SMOOTH = 2, OP_RESTRICT = 3, OP_SMOOTH1 = 4 };
+//   OP_SMOOTH1E: the same with b read from an external vector of the level's type
+enum { OP_APPLY = 0, OP_RESID = 1, OP_SMOOTH = 2, OP_RESTRICT = 3, OP_SMOOTH1 = 4, OP_SMOOTH1E = 5 };
 
 // First pre-sweep from x = 0: x = w D^-1 b; optionally keep b in type T.
 template <class TB, class T>
@@ -1638,6 +1639,7 @@ static double op_bytes(const Batch* b, int l, int lmode, int op) {
   if (op == OP_RESTRICT) return 2 * vec + mat + vec / 8.0;
   // the fused first sweeps read b in FP64 and the node blocks, write x and b's copy
   if (op == OP_SMOOTH1) return 3.0 * nodes * 8.0 + 9.0 * nodes * sizeof(T) + mat + 2 * vec;
+  if (op == OP_SMOOTH1E) return 9.0 * nodes * sizeof(T) + mat + 3 * vec;
   return nvec * vec + mat + dinv;
 }
 
@@ -1666,14 +1668,14 @@ template <class T, int OP>
 // (y: slot of level l, or for OP_RESTRICT the right-hand-side slot of level
 // l + 1, with y2 that level's first-sweep slot)
 static void vc_op(Batch* b, int l, int x, int bs, int y, T om, hipStream_t s, int mf = 0, int y2 = -1,
-                  int vbs = 0) {
+                  int vbs = 0, const void* eb = nullptr, void* ey = nullptr) {
   const DevList& dl = (OP == OP_RESTRICT) ? b->zm_r[l] : b->zm_s[l];
   if (l == 0 && mf)
     TG_TIMED(TG_KT_VCYCLE_FINE, (op_bytes<T>(b, 0, 1, OP)),
-             launch_fine_mfma(b, dl, OP, mf == 2, x, nullptr, bs, nullptr, y, nullptr, (double)om, false, s, y2));
+             launch_fine_mfma(b, dl, OP, mf == 2, x, nullptr, bs, eb, y, ey, (double)om, false, s, y2));
   else if (l == 0)
     TG_TIMED(TG_KT_VCYCLE_FINE, (op_bytes<T>(b, 0, 1, OP)),
-             launch_fine<T>(b, dl, 0, OP, x, nullptr, bs, nullptr, y, nullptr, (double)om, s, y2));
+             launch_fine<T>(b, dl, 0, OP, x, nullptr, bs, eb, y, ey, (double)om, s, y2));
   else
     TG_TIMED(TG_KT_VCYCLE_COARSE, (op_bytes<T>(b, l, 1, OP)),
              launch_fine<T>(b, dl, l, OP, x, nullptr, bs, nullptr, y, nullptr, (double)om, s, y2, vbs));
@@ -1701,7 +1703,11 @@ static int vcycle_t(Batch* b, int in_is_f32, int sb, const void* eb, int out_is_
   // directly and the last sweep writes the FP64 output.
   bool all_multi = true;
   for (int p : b->active) all_multi = all_multi && b->grids[p]->nlev > 1;
-  const bool fast_in = !in_is_f32 && sb >= 0 && all_multi;
+  // An external vector (of type T) is read and written by the same two sweeps;
+  // it may be one vector, since only the first of them reads the input.
+  const bool ext_in = sb < 0 && in_is_f32 == (f64 ? 0 : 1) && all_multi && mg.nu_pre >= 2 && in_scale < 0;
+  const bool ext_out = sy < 0 && out_is_f32 == (f64 ? 0 : 1) && all_multi && mg.nu_post >= 1;
+  const bool fast_in = (!in_is_f32 && sb >= 0 && all_multi) || ext_in;
   const bool fast_out = !out_is_f32 && sy >= 0 && all_multi;
   // The bottom of the cycle (each problem's levels from its vb_lb down) runs
   // as one launch between the two passes; the level-by-level launches skip
@@ -1739,7 +1745,8 @@ static int vcycle_t(Batch* b, int in_is_f32, int sb, const void* eb, int out_is_
     int it0 = 1;
     if (l == 0 && fast_in && mg.nu_pre >= 2) {
       // first sweep from zero computed while staging, second sweep in the same pass
-      vc_op<T, OP_SMOOTH1>(b, 0, in_scale, sb, o, om, s, mf, Bs, vbs);
+      if (ext_in) vc_op<T, OP_SMOOTH1E>(b, 0, -1, -1, o, om, s, mf, Bs, vbs, eb);
+      else vc_op<T, OP_SMOOTH1>(b, 0, in_scale, sb, o, om, s, mf, Bs, vbs);
       std::swap(c, o);
       it0 = 2;
     } else if (l == 0 && fast_in)
@@ -1773,6 +1780,11 @@ static int vcycle_t(Batch* b, int in_is_f32, int sb, const void* eb, int out_is_
     TG_TIMED(TG_KT_TRANSFER, 3.0 * nodes * 2 * sT + 3.0 * nodes / 8 * sT,
              k_prolong<T><<<nblk(sm), 256, 0, s>>>(b->desc_d, sm.ptr, l, c, FIN, nullptr, nullptr, vbs));
     for (int it = 0; it < mg.nu_post; ++it) {
+      if (l == 0 && ext_out && it == mg.nu_post - 1) {
+        vc_op<T, OP_SMOOTH>(b, 0, c, Bs, -1, om, s, mf, -1, vbs, nullptr, ey);
+        c = -1;   // result is in the external vector
+        break;
+      }
       if (l == 0 && fast_out && it == mg.nu_post - 1) {
         if (f64)
           vc_op<T, OP_SMOOTH>(b, 0, c, Bs, sy, om, s, 0, -1, vbs);   // straight into the FP64 output slot
@@ -1792,7 +1804,7 @@ static int vcycle_t(Batch* b, int in_is_f32, int sb, const void* eb, int out_is_
     cur[l] = c;
   }
   // ---- output (level 0): result in FIN0 for every problem
-  if (b->node[0].n && !fast_out) {
+  if (b->node[0].n && !fast_out && !ext_out) {
     level_sums(b, 0, 0, nodes, elems, c2);
     if (out_is_f32)
       TG_TIMED(TG_KT_TRANSFER, 3.0 * nodes * (sOut + sT),
