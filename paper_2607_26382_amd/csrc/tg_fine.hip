@@ -33,13 +33,17 @@ namespace tg {
 __host__ __device__ __forceinline__ float mad_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __host__ __device__ __forceinline__ double mad_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-enum { FOP_APPLY = 0, FOP_RESID = 1, FOP_SMOOTH = 2, FOP_RESTRICT = 3, FOP_SMOOTH1 = 4, FOP_SMOOTH1E = 5 };
+enum { FOP_APPLY = 0, FOP_RESID = 1, FOP_SMOOTH = 2, FOP_RESTRICT = 3, FOP_SMOOTH1 = 4, FOP_SMOOTH1E = 5,
+       FOP_SMOOTHP = 6 };
 // FOP_SMOOTH1 (level 0): the first two sweeps from x = 0 in one pass.  The
 // right-hand side is read from an FP64 slot (sb), times the per-problem scale
 // small[sx] when sx >= 0; every staged node gets x = w D^-1 b on the fly (the
 // first sweep), the output is the second sweep x + w D^-1 (b - K x), and the
 // FP32 copy of b that later sweeps read goes to slot sy2.  FOP_SMOOTH1E: the
 // same with b read from the external vector eb_ of type T, unscaled.
+// FOP_SMOOTHP: a smoothing sweep of x + P e, e the next level's vector in slot
+// sy2: the tile's coarse nodes are held in LDS and every staged node is
+// corrected there, in place of a prolongation pass over x.
 
 // Tiling of the residual sweep fused with the restriction (OP = FOP_RESTRICT):
 // a tile owns 7 x 7 coarse node columns and m coarse node layers, and computes
@@ -337,6 +341,10 @@ __device__ __forceinline__ const T* fvec(const LevelDesc& L, int slot, const voi
 
 #define FZ_TX 16
 #define FZ_OUT 15
+// FOP_SMOOTHP: coarse nodes per dimension that the 17 x 17 fine node columns
+// of a tile interpolate from, and coarse layers for zc + 2 fine layers
+#define FZ_C 10
+__host__ __device__ __forceinline__ int fz_coarse_layers(int zc) { return (zc + 2) / 2 + 2; }
 
 // Workgroup barrier for LDS traffic only: waits for this wave's LDS operations
 // (lgkmcnt) and synchronizes, leaving global loads in flight (a plain
@@ -382,6 +390,10 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
   // lane groups of a half-wave then use disjoint banks)
   constexpr int SSP = MF ? 260 : FZ_TX * FZ_TX;
   __shared__ T ss[MF ? 16 : 12][SSP];
+  // FOP_SMOOTHP: the tile's coarse nodes, 3 components each, layer by layer
+  extern __shared__ __align__(16) unsigned char fz_smem[];
+  T* sc = (T*)fz_smem;
+  constexpr bool SP = (OP == FOP_SMOOTHP);
   MfmaA mfA;
   const int2 wi = work[xcd_tile(blockIdx.x, gridDim.x)];
   const ProbDesc& P = probs[wi.x];
@@ -507,6 +519,48 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
       }
     }
   };
+  // FOP_SMOOTHP: coarse nodes from (cx0, cy0, cz0) on (those outside the coarse
+  // grid hold 0 and get weight 0)
+  const int cx0 = (x0 - 1) >> 1, cy0 = (y0 - 1) >> 1, cz0 = (z0 - 1) >> 1;
+  if constexpr (SP) {
+    const LevelDesc& Lc = P.lv[l + 1];
+    const auto* e = gp(fvec<T>(Lc, sy2, nullptr));
+    const int nl = ((zend + 1) >> 1) - cz0 + 1;
+    for (int q = threadIdx.x; q < nl * FZ_C * FZ_C * 3; q += 256) {
+      const int c = q % 3, m = q / 3, I = m % FZ_C + cx0, t = m / FZ_C, J = t % FZ_C + cy0, K = t / FZ_C + cz0;
+      const bool in = I >= 0 && I < Lc.NX && J >= 0 && J < Lc.NY && K >= 0 && K < Lc.NZ;
+      sc[q] = in ? e[3LL * (I + (long long)Lc.NX * (J + (long long)Lc.NY * K)) + c] : T(0);
+    }
+  }
+  // a += (P e) at fine node (i, j, k) (trilinear, corners in the order x, y, z)
+  auto correct = [&](int i, int j, int k, T& a0, T& a1, T& a2) {
+    const int I0 = (i >> 1) - cx0, J0 = (j >> 1) - cy0, K0 = (k >> 1) - cz0;
+    const int pi = i & 1, pj = j & 1, pk = k & 1;
+    const T w = (pi ? T(0.5) : T(1)) * (pj ? T(0.5) : T(1)) * (pk ? T(0.5) : T(1));
+    T s0 = T(0), s1 = T(0), s2 = T(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      if ((c & 4) && !pk) break;   // k is uniform
+      const int I = I0 + (c & 1 & pi), J = J0 + ((c >> 1) & pj), K = K0 + (c >> 2);
+      const T wc = (((c & 1) && !pi) || ((c & 2) && !pj)) ? T(0) : w;
+      const T* e = sc + 3 * ((K * FZ_C + J) * FZ_C + I);
+      s0 = mad_(wc, e[0], s0);
+      s1 = mad_(wc, e[1], s1);
+      s2 = mad_(wc, e[2], s2);
+    }
+    a0 += s0;
+    a1 += s1;
+    a2 += s2;
+  };
+  auto corrected = [&](Pre r, int k) -> Pre {
+    if constexpr (SP) {
+      if (k >= 0 && k < NZ) {
+        if (own_col) correct(ni, nj, k, r.a0, r.a1, r.a2);
+        if (ext_col) correct(exi, exj, k, r.e0, r.e1, r.e2);
+      }
+    }
+    return r;
+  };
   // State carried from one element layer to the next: the shared face in the
   // form the contraction takes it (face-mode for the vector forms, raw node
   // values for the matrix-core forms), the previous layer's top-face outputs,
@@ -527,6 +581,10 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
 #pragma unroll
   for (int q = 0; q < 16; ++q) s0.cr[q] = T(0);
   Pre pre = fetch(z0 - 1);
+  if constexpr (SP) {
+    lds_barrier();           // the coarse nodes
+    pre = corrected(pre, z0 - 1);
+  }
   stage(pre, z0 - 1);
   s0.bo[0] = pre.b0;
   s0.bo[1] = pre.b1;
@@ -567,6 +625,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
   // for layer k + 1
   auto step = [&](const int k, St& A, St& B) {
     const T own0 = A.own[0], own1 = A.own[1], own2 = A.own[2];   // node (ni, nj, k)
+    pre = corrected(pre, k + 1);
     if constexpr (MF) {
       B.own[0] = pre.a0;     // node (ni, nj, k + 1)
       B.own[1] = pre.a1;
@@ -595,7 +654,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
       const auto* bb = gp(fvec<T>(L, sb, eb_)) + 3 * n;
       rb0 = bb[0]; rb1 = bb[1]; rb2 = bb[2];
     }
-    if ((OP == FOP_SMOOTH || S1) && out_now) {
+    if ((OP == FOP_SMOOTH || SP || S1) && out_now) {
       const auto* Dp = gp(fD<T>(L)) + 9 * n;
 #pragma unroll
       for (int q = 0; q < 9; ++q) D[q] = Dp[q];
@@ -1005,6 +1064,24 @@ template <class T> static ModeCoef<T> mcoef(const tg_grid* g);
 template <> ModeCoef<double> mcoef<double>(const tg_grid* g) { return g->mc64; }
 template <> ModeCoef<float> mcoef<float>(const tg_grid* g) { return g->mc32; }
 
+// Tallest tile that the running problems take at level l, and whether the
+// first post-sweep there forms x + P e itself (FOP_SMOOTHP).  Up to 8 layers
+// its coarse nodes add at most 9 KB (FP32) of LDS to the 27 KB of the sweep;
+// taller tiles (full devices) would lose workgroups per CU, and keep the
+// separate pass.  At 64x32x32 (split BF16) the two prolongations took 4.4 us
+// and the sweeps after them 6.2 and 5.3, the prolonging sweeps take 8.7 and 7.9.
+#define FZ_SP_MAX 8
+static int fz_height(const Batch* b, int l) {
+  int h = 0;
+  for (int p : b->active)
+    if (l < b->grids[p]->nlev - 1) h = std::max(h, zm_height(b->grids[p]->lv[l].ez + 1, batch_zc_run(b, p, l)));
+  return h;
+}
+bool fine_prolongs(const Batch* b, int l) { return fz_height(b, l) <= FZ_SP_MAX; }
+static size_t fz_coarse_bytes(const Batch* b, int l, size_t tsize) {
+  return (size_t)fz_coarse_layers(fz_height(b, l)) * FZ_C * FZ_C * 3 * tsize;
+}
+
 // OP: 0 apply, 1 residual, 2 smoothing sweep on level l with the z-march
 // kernel (level 0: E Ke; levels 1..TG_MF_LEVELS: matrix-free Galerkin; deeper
 // levels: stored mode-basis Galerkin elements).
@@ -1016,13 +1093,16 @@ int launch_fine(const Batch* b, const DevList& dl, int l, int op, int sx, const 
   const ModeCoef<T> mc = mcoef<T>(b->grids[0]);
   const ProbDesc* desc = b->desc_d;
   const T om = T(omega);
+  // (dynamic LDS: the coarse nodes of a prolonging sweep)
+  const size_t dyn = op == FOP_SMOOTHP ? fz_coarse_bytes(b, l, sizeof(T)) : 0;
 #define TG_ZMOP(OPV, KV) \
-  k_fine_zm<T, OPV, KV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip)
+  k_fine_zm<T, OPV, KV><<<dl.n, 256, dyn, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip)
 #define TG_ZM(KV)                                        \
   do {                                                   \
     if (op == FOP_APPLY) TG_ZMOP(FOP_APPLY, KV);         \
     else if (op == FOP_RESID) TG_ZMOP(FOP_RESID, KV);    \
     else if (op == FOP_SMOOTH) TG_ZMOP(FOP_SMOOTH, KV);  \
+    else if (op == FOP_SMOOTHP) TG_ZMOP(FOP_SMOOTHP, KV); \
     else TG_ZMOP(FOP_RESTRICT, KV);                      \
   } while (0)
   const bool first = op == FOP_SMOOTH1 || op == FOP_SMOOTH1E;
@@ -1051,8 +1131,9 @@ int launch_fine_mfma(const Batch* b, const DevList& dl, int op, bool split, int 
   const ModeCoef<float> mc = mcoef<float>(b->grids[0]);
   const ProbDesc* desc = b->desc_d;
   const float om = float(omega);
+  const size_t dyn = op == FOP_SMOOTHP ? fz_coarse_bytes(b, 0, sizeof(float)) : 0;
 #define TG_MF(OPV, K, TYV) \
-  k_fine_zm<float, OPV, K, TYV><<<dl.n, 256, 0, s>>>(desc, dl.ptr, 0, sx, ex, sb, eb, sy, ey, sy2, om, mc, 0)
+  k_fine_zm<float, OPV, K, TYV><<<dl.n, 256, dyn, s>>>(desc, dl.ptr, 0, sx, ex, sb, eb, sy, ey, sy2, om, mc, 0)
   if (out64) {
     if (split) TG_MF(FOP_SMOOTH, 3, double); else TG_MF(FOP_SMOOTH, 2, double);
   } else if (op == FOP_APPLY) {
@@ -1061,6 +1142,8 @@ int launch_fine_mfma(const Batch* b, const DevList& dl, int op, bool split, int 
     if (split) TG_MF(FOP_RESID, 3, float); else TG_MF(FOP_RESID, 2, float);
   } else if (op == FOP_SMOOTH) {
     if (split) TG_MF(FOP_SMOOTH, 3, float); else TG_MF(FOP_SMOOTH, 2, float);
+  } else if (op == FOP_SMOOTHP) {
+    if (split) TG_MF(FOP_SMOOTHP, 3, float); else TG_MF(FOP_SMOOTHP, 2, float);
   } else if (op == FOP_SMOOTH1) {
     if (split) TG_MF(FOP_SMOOTH1, 3, float); else TG_MF(FOP_SMOOTH1, 2, float);
   } else if (op == FOP_SMOOTH1E) {
@@ -1111,7 +1194,9 @@ struct VbThreads {
 // LDS words (of type T) the bottom needs from level lb of grid g down
 static size_t vb_words(const tg_grid* g, int lb) {
   const auto& H = g->lv[lb];
-  size_t w = (size_t)24 * H.n_elem;                     // element outputs
+  // element outputs; the coarsest solve's scratch (nine words per row, in 64s) in their place
+  const size_t w_solve = (size_t)9 * 64 * ((g->ncoarse + 63) / 64);
+  size_t w = std::max(24 * (size_t)H.n_elem, w_solve);
   w += 3 * (size_t)H.n_nodes;                           // residual
   for (int l = lb; l < g->nlev; ++l) w += 6 * (size_t)g->lv[l].n_nodes;   // x, b
   return w;
@@ -1332,30 +1417,35 @@ __device__ void vb_prolong(const VbLev<T>& F, const VbLev<T>& C) {
 }
 
 // x = K_c^-1 b on the free DOFs of the coarsest level (free index
-// 3 ((NX - 1) t + i - 1) + c of node i + NX t): eight lanes per row, each
-// summing every eighth column, then a fixed butterfly over the eight
+// 3 ((NX - 1) t + i - 1) + c of node i + NX t).  A wave takes 64 rows and one
+// eighth of the columns (every eighth); the eight sums of a row are added
+// pairwise through LDS.  The inverse is symmetric, so the rows are read as
+// columns, 64 consecutive entries at a time; eight lanes side by side in a row
+// took 16.8 us at n = 288 (FP64) and 3.4 at 108 (FP32), this 11.9 and 2.5.
+// buf: n + 8 x 64 x (rows / 64, rounded up) words of scratch.
 template <class T>
-__device__ void vb_coarse(const ProbDesc& P, const VbLev<T>& C) {
-  const int n = P.ncoarse;
+__device__ void vb_coarse(const ProbDesc& P, const VbLev<T>& C, T* buf) {
+  const int n = P.ncoarse, ng = (n + 63) >> 6;
   const T TG_GLOBAL* Ci = gp(vb_cinv<T>(P));
-  const int part = threadIdx.x & 7, row0 = threadIdx.x >> 3;
-  const int NXm = C.NX - 1;
-  for (int q0 = 0; q0 < n; q0 += (int)blockDim.x / 8) {
-    const int q = q0 + row0;
+  const int NXm = C.NX - 1, lane = threadIdx.x & 63;
+  auto node_of = [&](int q) { const int f = q / 3, t = f / NXm; return 3 * (f - t * NXm + 1 + C.NX * t) + q - 3 * f; };
+  T* sb = buf;                  // b by free index
+  T* sp = buf + 64 * ng;        // partial sums: part, row
+  for (int q = threadIdx.x; q < n; q += (int)blockDim.x) sb[q] = C.b[node_of(q)];
+  __syncthreads();
+  for (int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < 8 * ng; w += (int)blockDim.x >> 6) {
+    const int part = w & 7, q = (w >> 3) * 64 + lane;
     T s = T(0);
-    if (q < n)
-#pragma unroll 8
-      for (int c = part; c < n; c += 8) {
-        const int fn = c / 3, node = fn % NXm + 1 + C.NX * (fn / NXm);
-        s = mad_(Ci[(long long)q * n + c], C.b[3 * node + c % 3], s);
-      }
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    s += __shfl_xor(s, 4, 64);
-    if (q < n && part == 0) {
-      const int fn = q / 3, node = fn % NXm + 1 + C.NX * (fn / NXm);
-      C.x[3 * node + q % 3] = s;
-    }
+    const T TG_GLOBAL* col = Ci + min(q, n - 1);
+#pragma unroll 16
+    for (int c = part; c < n; c += 8) s = mad_(col[(long long)c * n], sb[c], s);
+    sp[part * 64 * ng + q] = s;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < n; q += (int)blockDim.x) {
+    const T* p = sp + q;
+    const int st = 64 * ng;
+    C.x[node_of(q)] = ((p[0] + p[st]) + (p[2 * st] + p[3 * st])) + ((p[4 * st] + p[5 * st]) + (p[6 * st] + p[7 * st]));
   }
   __syncthreads();
 }
@@ -1373,7 +1463,7 @@ __global__ __launch_bounds__((VbThreads<T, L1>::N)) void k_vbottom(const ProbDes
   const int lb = sizeof(T) == 8 ? P.vb_lb64 : P.vb_lb32;
   const int Lc = P.nlev - 1;
   T* eb = (T*)vb_smem;
-  T* rbuf = eb + 24 * (P.lv[lb].ex * P.lv[lb].ey * P.lv[lb].ez);
+  T* rbuf = eb + max(24 * (P.lv[lb].ex * P.lv[lb].ey * P.lv[lb].ez), 9 * 64 * ((P.ncoarse + 63) / 64));
   // level l's x and b follow the element and residual buffers, level by level
   auto V = [&](int l) -> VbLev<T> {
     T* o = rbuf + 3 * P.lv[lb].n_nodes;
@@ -1405,7 +1495,7 @@ __global__ __launch_bounds__((VbThreads<T, L1>::N)) void k_vbottom(const ProbDes
     vb_sweep<T, true, L1>(P, l, Vl, eb, rbuf, omega);
     vb_restrict<T>(Vl, rbuf, P.lv[l + 1], V(l + 1), omega, l + 1 < Lc);
   }
-  vb_coarse<T>(P, V(Lc));
+  vb_coarse<T>(P, V(Lc), eb);
   // ascend
   for (int l = Lc - 1; l >= lb; --l) {
     const VbLev<T> Vl = V(l);

@@ -339,6 +339,9 @@ template <class T>
 // from zero into slot sy2
 int launch_fine(const Batch* b, const DevList& dl, int l, int op, int sx, const void* ex, int sb,
                 const void* eb, int sy, void* ey, double omega, hipStream_t s, int sy2 = -1, int vbskip = 0);
+// whether level l's first post-sweep takes the prolongation in (op 6, sy2 = the
+// next level's slot)
+bool fine_prolongs(const Batch* b, int l);
 // the bottom of the V-cycle in one launch per problem (levels vb_lb.. in LDS)
 int vbottom_level(const tg_grid* g, size_t tsize, size_t lds);
 size_t vbottom_lds_limit();

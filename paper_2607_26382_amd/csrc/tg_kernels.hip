@@ -554,7 +554,9 @@ __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* _
 //   OP_SMOOTH1: level 0, the first two sweeps from x = 0 with b read from an
 //               FP64 slot (x = scale offset, y2 = slot of b's FP32 copy)
 //   OP_SMOOTH1E: the same with b read from an external vector of the level's type
-enum { OP_APPLY = 0, OP_RESID = 1, OP_SMOOTH = 2, OP_RESTRICT = 3, OP_SMOOTH1 = 4, OP_SMOOTH1E = 5 };
+//   OP_SMOOTHP: OP_SMOOTH of x + P e (y2 = slot of e at the next level)
+enum { OP_APPLY = 0, OP_RESID = 1, OP_SMOOTH = 2, OP_RESTRICT = 3, OP_SMOOTH1 = 4, OP_SMOOTH1E = 5,
+       OP_SMOOTHP = 6 };
 
 // First pre-sweep from x = 0: x = w D^-1 b; optionally keep b in type T.
 template <class TB, class T>
@@ -1633,14 +1635,14 @@ static double op_bytes(const Batch* b, int l, int lmode, int op) {
   // fine level and matrix-free Galerkin levels read the fine moduli; deeper
   // levels read their stored mode-basis element matrices
   const double mat = (l <= TG_MF_LEVELS) ? elems * double(1 << (3 * l)) * sizeof(T) : elems * double(TG_GM_NU) * sizeof(T);
-  const double dinv = (op == OP_SMOOTH) ? 9.0 * nodes * sizeof(T) : 0.0;
+  const double dinv = (op == OP_SMOOTH || op == OP_SMOOTHP) ? 9.0 * nodes * sizeof(T) : 0.0;
   const int nvec = op == OP_APPLY ? 2 : 3;
   // the fused restriction reads x and b and writes the coarse right-hand side
   if (op == OP_RESTRICT) return 2 * vec + mat + vec / 8.0;
   // the fused first sweeps read b in FP64 and the node blocks, write x and b's copy
   if (op == OP_SMOOTH1) return 3.0 * nodes * 8.0 + 9.0 * nodes * sizeof(T) + mat + 2 * vec;
   if (op == OP_SMOOTH1E) return 9.0 * nodes * sizeof(T) + mat + 3 * vec;
-  return nvec * vec + mat + dinv;
+  return nvec * vec + mat + dinv + (op == OP_SMOOTHP ? vec / 8.0 : 0.0);
 }
 
 int k_apply(Batch* b, int prec, int sx, const void* ex, int sy, void* ey, hipStream_t s) {
@@ -1777,9 +1779,18 @@ static int vcycle_t(Batch* b, int in_is_f32, int sb, const void* eb, int out_is_
     int c = cur[l];
     int o = (c == XA) ? XB : XA;
     level_sums(b, l, 1, nodes, elems, c2);
-    TG_TIMED(TG_KT_TRANSFER, 3.0 * nodes * 2 * sT + 3.0 * nodes / 8 * sT,
-             k_prolong<T><<<nblk(sm), 256, 0, s>>>(b->desc_d, sm.ptr, l, c, FIN, nullptr, nullptr, vbs));
+    // the first post-sweep forms x + P e itself (not where it is level 0's last
+    // sweep, which writes the output)
+    const bool pro = mg.nu_post >= (l == 0 ? 2 : 1) && fine_prolongs(b, l);
+    if (!pro)
+      TG_TIMED(TG_KT_TRANSFER, 3.0 * nodes * 2 * sT + 3.0 * nodes / 8 * sT,
+               k_prolong<T><<<nblk(sm), 256, 0, s>>>(b->desc_d, sm.ptr, l, c, FIN, nullptr, nullptr, vbs));
     for (int it = 0; it < mg.nu_post; ++it) {
+      if (it == 0 && pro) {
+        vc_op<T, OP_SMOOTHP>(b, l, c, Bs, o, om, s, mf, FIN, vbs);
+        std::swap(c, o);
+        continue;
+      }
       if (l == 0 && ext_out && it == mg.nu_post - 1) {
         vc_op<T, OP_SMOOTH>(b, 0, c, Bs, -1, om, s, mf, -1, vbs, nullptr, ey);
         c = -1;   // result is in the external vector
