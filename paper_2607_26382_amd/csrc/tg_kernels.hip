@@ -979,14 +979,20 @@ __global__ __launch_bounds__(256) void k_update_dots_reg_(const ProbDesc* __rest
 struct SmallOffs {
   int mmax, H, g, cs, sn, y, h, tmp, scal, hist;
 };
-// the scalar parts of a delayed-CGS2 step, run by one wave (defined below)
-__device__ void dcgs_a_wave(const ProbDesc& P, int p, const SmallOffs& o, int j, double* status_out);
-__device__ void dcgs_b_wave(const ProbDesc& P, int p, const SmallOffs& o, int j, int cap, double tol, double brk,
-                            double* status_out);
-
 // CGS2 with delayed reorthogonalization, sweep A.  For k < nv the chunk
 // partials of V_k . q and V_k . w, then q . q, q . w, w . w: 2 nv + 3 entries
 // in the order [V.q (nv) | V.w (nv) | q.q, q.w, w.w].  One read of V, q, w.
+// NT (both sweeps): V is read with non-temporal loads.  A basis that exceeds
+// the L2 caches is not read again before it is evicted, and without the hint
+// it also evicts what the V-cycle reads next: over the policy step of 24 64x32x32
+// states sweep A went from 97 to 89 us per launch, B from 103 to 98.  One
+// state's basis (29 MB at 15 vectors) stays cached, and is read the ordinary
+// way (10 us against 13).
+template <bool NT, class P>
+__device__ __forceinline__ double basis_load(P p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool NT>
 __global__ __launch_bounds__(256) void k_dots2_(const ProbDesc* __restrict__ probs,
                                                 const int2* __restrict__ work, int sbase, int nv, int sq,
                                                 int sw) {
@@ -1026,7 +1032,7 @@ __global__ __launch_bounds__(256) void k_dots2_(const ProbDesc* __restrict__ pro
         const auto* v = gp(L.vec64 + (long long)(sbase + k) * L.stride);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-          const double x = v[lo + threadIdx.x + 256LL * q];
+          const double x = basis_load<NT>(v + (lo + threadIdx.x + 256LL * q));
           a[g] += x * qr[q];
           c[g] += x * wr[q];
         }
@@ -1073,6 +1079,7 @@ __global__ __launch_bounds__(256) void k_dots2_(const ProbDesc* __restrict__ pro
 //   qnext <- w - sum_k c_k V_k - cw * q_old (the next vector, projected once)
 // with a = coef[0, nv), c = coef[nv, 2 nv), cq = coef[2 nv], cw = coef[2 nv + 1];
 // chunk partial of qnext . qnext into part row 0.  One read of V, q, w.
+template <bool NT>
 __global__ __launch_bounds__(256) void k_update2_(const ProbDesc* __restrict__ probs,
                                                   const int2* __restrict__ work, int sbase, int nv, int sq,
                                                   int sw, int snext, int coef_off) {
@@ -1094,7 +1101,7 @@ __global__ __launch_bounds__(256) void k_update2_(const ProbDesc* __restrict__ p
     const auto* v = gp(L.vec64 + (long long)(sbase + k) * L.stride);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const double x = v[lo + threadIdx.x + 256LL * q];
+      const double x = basis_load<NT>(v + (lo + threadIdx.x + 256LL * q));
       ta[q] += ak * x;
       tc[q] += ck * x;
     }
@@ -1247,27 +1254,43 @@ __global__ void k_arnoldi_(const ProbDesc* __restrict__ probs, const int2* __res
 // coefficients), replacing the tentative column and rotation of step j-1.
 // The first-pass coefficients of column j are h1 = [Q^T w ; q_j . w]; the
 // coefficients of sweep B go to tmp (see k_update2_).
-__device__ void dcgs_a_wave(const ProbDesc& P, int p, const SmallOffs& o, int j, double* status_out) {
-  // one wave: the column and the rotations are read in parallel and rotated
-  // in LDS by lane 0 (a chain of register operations rather than of round
-  // trips through memory)
-  __shared__ double sH[TG_MAX_RESTART + 2], sC[TG_MAX_RESTART + 1], sS[TG_MAX_RESTART + 1];
-  __shared__ int bad;
-  const int2 wi = make_int2(p, 0);
+// The scalar state a part reads, in LDS: loaded by the workgroup while the
+// chunk sums are formed, so that the one wave that runs the part does not wait
+// for memory in between.
+struct FinState {
+  double h[TG_MAX_RESTART + 2], c[TG_MAX_RESTART + 1], s[TG_MAX_RESTART + 1];
+  double sc[16];                // scalars SC_*
+  double tmp[TG_PART_W];        // chunk sums
+  int bad;
+};
+__device__ __forceinline__ void fin_load(const ProbDesc& P, const SmallOffs& o, int nh, int nrot, FinState& F) {
+  const auto* S = gp((const double*)P.small);
+  for (int i = threadIdx.x; i < nh; i += (int)blockDim.x) F.h[i] = S[o.h + i];
+  for (int i = threadIdx.x; i < nrot; i += (int)blockDim.x) {
+    F.c[i] = S[o.cs + i];
+    F.s[i] = S[o.sn + i];
+  }
+  if (threadIdx.x < 16) F.sc[threadIdx.x] = S[o.scal + threadIdx.x];
+}
+
+__device__ void dcgs_a_wave(const ProbDesc& P, int p, const SmallOffs& o, int j, FinState& F, double* status_out) {
+  // one wave: the column and the rotations are rotated in LDS by lane 0 (a
+  // chain of register operations rather than of round trips through memory)
   const int lane = threadIdx.x;
   double* S = P.small;
   double* sc = S + o.scal;
-  if (sc[SC_STATUS] != TG_RUNNING) return;
+  if (F.sc[SC_STATUS] != TG_RUNNING) return;
+  const double* T = F.tmp;
   double* tmp = S + o.tmp;
   double* h1 = S + o.h;
   const int ldh = o.mmax + 1;
-  const double rho = sc[SC_RHO];
-  const double alpha = tmp[2 * j] / (rho * rho), qw = tmp[2 * j + 1] / rho, ww = tmp[2 * j + 2];
+  const double rho = F.sc[SC_RHO];
+  const double alpha = T[2 * j] / (rho * rho), qw = T[2 * j + 1] / rho, ww = T[2 * j + 2];
   double ss = 0.0, sz = 0.0;
   for (int k = lane; k < j; k += 64) {
-    const double sk = tmp[k] / rho;
+    const double sk = T[k] / rho;
     ss += sk * sk;
-    sz += sk * tmp[j + k];
+    sz += sk * T[j + k];
   }
   ss = wave_sum(ss);
   sz = wave_sum(sz);
@@ -1278,52 +1301,49 @@ __device__ void dcgs_a_wave(const ProbDesc& P, int p, const SmallOffs& o, int j,
   if (st != TG_RUNNING) {
     if (lane == 0) {
       sc[SC_STATUS] = st;
-      status_out[wi.x] = st;
+      status_out[p] = st;
     }
     return;
   }
   const double nu = sqrt(nu2);
   if (lane == 0) sc[SC_FLAG] = ww;
   if (j >= 1) {
+    double* sH = F.h;
     double* Hc = S + o.H + (long long)ldh * (j - 1);
-    for (int i = lane; i < j; i += 64) sH[i] = h1[i] + tmp[i];
-    for (int i = lane; i < j - 1; i += 64) {
-      sC[i] = S[o.cs + i];
-      sS[i] = S[o.sn + i];
-    }
+    for (int i = lane; i < j; i += 64) sH[i] = sH[i] + T[i];
     TG_WAVE_SYNC();
     if (lane == 0) {
       sH[j] = rho * nu;
       double carry = sH[0];
       for (int i = 0; i < j - 1; ++i) {
-        const double c = sC[i], sn = sS[i], b = sH[i + 1];
+        const double c = F.c[i], sn = F.s[i], b = sH[i + 1];
         sH[i] = c * carry + sn * b;
         carry = -sn * carry + c * b;
       }
       sH[j - 1] = carry;
       const double d = hypot(sH[j - 1], sH[j]);
-      bad = !(d > 0.0) || !isfinite(d);
-      if (bad) {
+      F.bad = !(d > 0.0) || !isfinite(d);
+      if (F.bad) {
         sc[SC_STATUS] = TG_NONFINITE;
-        status_out[wi.x] = TG_NONFINITE;
+        status_out[p] = TG_NONFINITE;
       } else {
         const double c = sH[j - 1] / d, sn = sH[j] / d;
         S[o.cs + j - 1] = c;
         S[o.sn + j - 1] = sn;
         sH[j - 1] = d;
         sH[j] = 0.0;
-        const double gj = sc[SC_GJ];
+        const double gj = F.sc[SC_GJ];
         S[o.g + j - 1] = c * gj;
         S[o.g + j] = -sn * gj;
       }
     }
     TG_WAVE_SYNC();
     for (int i = lane; i <= j; i += 64) Hc[i] = sH[i];
-    if (bad) return;
+    if (F.bad) return;
   }
   const double hjj = (qw - sz) / nu;
   for (int k = lane; k < j; k += 64) {
-    const double sk = tmp[k] / rho, zk = tmp[j + k];
+    const double sk = T[k] / rho, zk = T[j + k];
     h1[k] = zk;
     tmp[j + k] = zk - sk * hjj / nu;
     tmp[k] = sk / nu;
@@ -1340,34 +1360,24 @@ __device__ void dcgs_a_wave(const ProbDesc& P, int p, const SmallOffs& o, int j,
 // only after the next sweep A): rotations, projected residual estimate,
 // history and stop tests as in the immediate form.
 __device__ void dcgs_b_wave(const ProbDesc& P, int p, const SmallOffs& o, int j, int cap, double tol, double brk,
-                            double* status_out) {
-  __shared__ double sH[TG_MAX_RESTART + 2], sC[TG_MAX_RESTART + 1], sS[TG_MAX_RESTART + 1];
-  __shared__ int bad;
-  const int2 wi = make_int2(p, 0);
+                            FinState& F, double* status_out) {
   const int lane = threadIdx.x;
   double* S = P.small;
   double* sc = S + o.scal;
-  if (sc[SC_STATUS] != TG_RUNNING) return;   // stopped in sweep A of this step
-  const double* h1 = S + o.h;
+  if (F.sc[SC_STATUS] != TG_RUNNING) return;   // stopped in sweep A of this step
   const int ldh = o.mmax + 1;
-  const double rn = sqrt(S[o.tmp]);
+  const double rn = sqrt(F.tmp[0]);
+  double* sH = F.h;
   double* Hc = S + o.H + (long long)ldh * j;
   bool finite = true;
-  for (int i = lane; i <= j; i += 64) {
-    sH[i] = h1[i];
-    finite = finite && isfinite(sH[i]);
-  }
-  for (int i = lane; i < j; i += 64) {
-    sC[i] = S[o.cs + i];
-    sS[i] = S[o.sn + i];
-  }
+  for (int i = lane; i <= j; i += 64) finite = finite && isfinite(sH[i]);
   finite = __all(finite) && isfinite(rn);
   if (!finite) {
     for (int i = lane; i <= j; i += 64) Hc[i] = sH[i];
     if (lane == 0) {
       Hc[j + 1] = rn;
       sc[SC_STATUS] = TG_NONFINITE;
-      status_out[wi.x] = TG_NONFINITE;
+      status_out[p] = TG_NONFINITE;
     }
     return;
   }
@@ -1376,16 +1386,16 @@ __device__ void dcgs_b_wave(const ProbDesc& P, int p, const SmallOffs& o, int j,
     sH[j + 1] = rn;
     double carry = sH[0];
     for (int i = 0; i < j; ++i) {
-      const double c = sC[i], sn = sS[i], b = sH[i + 1];
+      const double c = F.c[i], sn = F.s[i], b = sH[i + 1];
       sH[i] = c * carry + sn * b;
       carry = -sn * carry + c * b;
     }
     sH[j] = carry;
     const double d = hypot(sH[j], sH[j + 1]);
-    bad = !(d > 0.0) || !isfinite(d);
-    if (bad) {
+    F.bad = !(d > 0.0) || !isfinite(d);
+    if (F.bad) {
       sc[SC_STATUS] = TG_NONFINITE;
-      status_out[wi.x] = TG_NONFINITE;
+      status_out[p] = TG_NONFINITE;
     } else {
       const double c = sH[j] / d, sn = sH[j + 1] / d;
       S[o.cs + j] = c;
@@ -1396,8 +1406,8 @@ __device__ void dcgs_b_wave(const ProbDesc& P, int p, const SmallOffs& o, int j,
       sc[SC_GJ] = gj;
       S[o.g + j + 1] = -sn * gj;
       S[o.g + j] = c * gj;
-      const int kk = (int)sc[SC_ITERS] + 1;   // iterations so far live on the device
-      const double est = fabs(S[o.g + j + 1]) / sc[SC_BNORM];
+      const int kk = (int)F.sc[SC_ITERS] + 1;   // iterations so far live on the device
+      const double est = fabs(-sn * gj) / F.sc[SC_BNORM];
       S[o.hist + kk] = est;
       sc[SC_EST] = est;
       sc[SC_ITERS] = kk;
@@ -1407,10 +1417,10 @@ __device__ void dcgs_b_wave(const ProbDesc& P, int p, const SmallOffs& o, int j,
       sc[SC_INV] = rn > 0.0 ? 1.0 / rn : 0.0;
       double st = TG_RUNNING;
       if (est <= tol) st = TG_PROJ_CONVERGED;
-      else if (rn <= brk * sqrt(fmax(sc[SC_FLAG], 0.0))) st = TG_BREAKDOWN;
+      else if (rn <= brk * sqrt(fmax(F.sc[SC_FLAG], 0.0))) st = TG_BREAKDOWN;
       else if (kk >= cap) st = TG_MAXIT;
       sc[SC_STATUS] = st;
-      status_out[wi.x] = st;
+      status_out[p] = st;
     }
   }
   TG_WAVE_SYNC();
@@ -1418,40 +1428,48 @@ __device__ void dcgs_b_wave(const ProbDesc& P, int p, const SmallOffs& o, int j,
 }
 
 // The scalar ends of the two sweeps of a delayed-CGS2 step, one workgroup per
-// problem: the chunk partials summed in a fixed order into small+tmp, then the
-// step's scalar part on one wave.  A: rows [V.q | V.w | q.q, q.w, w.w], each
-// summed over the chunks in chunk order; B: ||q_next||^2 over the chunks.
+// problem: the chunk partials summed in a fixed order, then the step's scalar
+// part on one wave.  A: rows [V.q | V.w | q.q, q.w, w.w], each summed over the
+// chunks in chunk order; B: ||q_next||^2 over the chunks.  Bound by latency:
+// with the scalar state read in turn after the sums, A took 9.3 us between the
+// sweeps of one 64x32x32 problem and 11.9 of 24, so 7.1 and 8.2 (B 4.7 and
+// 7.0, now 4.6 and 6.1).
 __global__ __launch_bounds__(256) void k_fin_a_(const ProbDesc* __restrict__ probs, const int2* __restrict__ work,
                                                 SmallOffs o, int j, double* status_out) {
+  __shared__ FinState F;
   const int2 wi = work[blockIdx.x];
   const ProbDesc& P = probs[wi.x];
   TG_GATE(P);
+  fin_load(P, o, j, j - 1, F);
   const int nc = P.lv[0].n_chunks;
-  double* tmp = P.small + o.tmp;
+  const auto* part = gp((const double*)P.part);
   for (int r = threadIdx.x; r < 2 * j + 3; r += 256) {
-    const double* pr = P.part + (long long)r * nc;
+    const auto* pr = part + (long long)r * nc;
     double a = 0.0;
-#pragma unroll 8
+#pragma unroll 32
     for (int c = 0; c < nc; ++c) a += pr[c];
-    tmp[r] = a;
+    F.tmp[r] = a;
   }
   __syncthreads();
-  if (threadIdx.x < 64) dcgs_a_wave(P, wi.x, o, j, status_out);
+  if (threadIdx.x < 64) dcgs_a_wave(P, wi.x, o, j, F, status_out);
 }
 __global__ __launch_bounds__(256) void k_fin_b_(const ProbDesc* __restrict__ probs, const int2* __restrict__ work,
                                                 SmallOffs o, int j, int cap, double tol, double brk,
                                                 double* status_out) {
   __shared__ double sh[4];
+  __shared__ FinState F;
   const int2 wi = work[blockIdx.x];
   const ProbDesc& P = probs[wi.x];
   TG_GATE(P);
+  fin_load(P, o, j + 1, j, F);
   const int nc = P.lv[0].n_chunks;
+  const auto* part = gp((const double*)P.part);
   double a = 0.0;
-  for (int c = threadIdx.x; c < nc; c += 256) a += P.part[c];
+  for (int c = threadIdx.x; c < nc; c += 256) a += part[c];
   a = block_sum256(a, sh);
-  if (threadIdx.x == 0) P.small[o.tmp] = a;
+  if (threadIdx.x == 0) F.tmp[0] = a;
   __syncthreads();
-  if (threadIdx.x < 64) dcgs_b_wave(P, wi.x, o, j, cap, tol, brk, status_out);
+  if (threadIdx.x < 64) dcgs_b_wave(P, wi.x, o, j, cap, tol, brk, F, status_out);
 }
 
 // Least squares: y = R^{-1} g over the jdone columns (back substitution).
@@ -1926,12 +1944,17 @@ int k_update_dots(Batch* b, int sbase, int nv, int sw, int coef_is_tmp, int ndot
   return check_launch("update_dots");
 }
 
+// Whether a sweep over nv basis vectors of the running problems exceeds the L2
+// caches (8 x 4 MB) well enough that non-temporal loads pay (k_dots2_).
+static bool basis_streams(const Batch* b, int nv) { return 8.0 * (nv + 2) * dofs0(b) > 64e6; }
+
 // Sweep A of the delayed CGS2 step j (nv = j basis vectors), then its
 // scalar end (chunk sums and the first scalar part) in one per-problem launch.
 int k_dots2(Batch* b, int sbase, int nv, int sq, int sw, hipStream_t s) {
   if (b->vec.n)
     TG_TIMED(TG_KT_MULTIDOT, 8.0 * (nv + 2) * dofs0(b),
-             k_dots2_<<<nblk(b->vec), 256, 0, s>>>(b->desc_d, b->vec.ptr, sbase, nv, sq, sw));
+             (basis_streams(b, nv) ? k_dots2_<true> : k_dots2_<false>)<<<nblk(b->vec), 256, 0, s>>>(
+                 b->desc_d, b->vec.ptr, sbase, nv, sq, sw));
   if (b->prob.n)
     TG_TIMED(TG_KT_SCALAR, 0, k_fin_a_<<<nblk(b->prob), 256, 0, s>>>(b->desc_d, b->prob.ptr, offs(b), nv, b->sc_d));
   return check_launch("dots2");
@@ -1943,7 +1966,8 @@ int k_update2(Batch* b, int sbase, int nv, int sq, int sw, int snext, int cap, d
   const SmallOffs o = offs(b);
   if (b->vec.n)
     TG_TIMED(TG_KT_UPDATE, 8.0 * (nv + 4) * dofs0(b),
-             k_update2_<<<nblk(b->vec), 256, 0, s>>>(b->desc_d, b->vec.ptr, sbase, nv, sq, sw, snext, o.tmp));
+             (basis_streams(b, nv) ? k_update2_<true> : k_update2_<false>)<<<nblk(b->vec), 256, 0, s>>>(
+                 b->desc_d, b->vec.ptr, sbase, nv, sq, sw, snext, o.tmp));
   if (b->prob.n)
     TG_TIMED(TG_KT_SCALAR, 0,
              k_fin_b_<<<nblk(b->prob), 256, 0, s>>>(b->desc_d, b->prob.ptr, o, nv, cap, tol, brk, b->sc_d));
