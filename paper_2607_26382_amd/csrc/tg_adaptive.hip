@@ -311,27 +311,54 @@ __global__ __launch_bounds__(AD_BLOCK) void k_st_div_norm(const double* __restri
 
 __global__ void k_st_sqrt(const double* __restrict__ ss, double* __restrict__ out) { *out = sqrt(*ss); }
 
-// x = omega D^-1 b node by node at one level (D the 3 x 3 diagonal block of
-// K at the node); the clamped nodes get 0
+// x = omega D^-1 (*scale b) node by node at one level (D the 3 x 3 diagonal
+// block of K at the node; scale NULL: 1); the clamped nodes get 0; bcopy (may be
+// NULL) receives *scale b
 __global__ __launch_bounds__(AD_BLOCK) void k_st_jacobi(const double* __restrict__ Dinv, const double* __restrict__ b,
-                                                        double* __restrict__ x, double omega, long long n_nodes,
+                                                        const double* __restrict__ scale, double* __restrict__ x,
+                                                        double* __restrict__ bcopy, double omega, long long n_nodes,
                                                         int NX) {
+  const double sc = scale ? *scale : 1.0;
   for (long long v = (long long)blockIdx.x * AD_BLOCK + threadIdx.x; v < n_nodes;
        v += (long long)gridDim.x * AD_BLOCK) {
-    const double b0 = b[3 * v], b1 = b[3 * v + 1], b2 = b[3 * v + 2];
-    const double* D = Dinv + 9 * v;
     const bool fixed = (v % NX) == 0;
+    const double b0 = fixed ? 0.0 : b[3 * v] * sc, b1 = fixed ? 0.0 : b[3 * v + 1] * sc,
+                 b2 = fixed ? 0.0 : b[3 * v + 2] * sc;
+    const double* D = Dinv + 9 * v;
+    if (bcopy) {
+      bcopy[3 * v] = b0;
+      bcopy[3 * v + 1] = b1;
+      bcopy[3 * v + 2] = b2;
+    }
     x[3 * v] = fixed ? 0.0 : omega * (D[0] * b0 + D[1] * b1 + D[2] * b2);
     x[3 * v + 1] = fixed ? 0.0 : omega * (D[3] * b0 + D[4] * b1 + D[5] * b2);
     x[3 * v + 2] = fixed ? 0.0 : omega * (D[6] * b0 + D[7] * b1 + D[8] * b2);
   }
 }
 
-// the momentum term of a Chebyshev step: y += beta (x - xp) (xp NULL: zero)
-__global__ __launch_bounds__(AD_BLOCK) void k_st_cheb_fix(double* __restrict__ y, const double* __restrict__ x,
-                                                          const double* __restrict__ xp, double beta, long long n) {
-  for (long long i = (long long)blockIdx.x * AD_BLOCK + threadIdx.x; i < n; i += (long long)gridDim.x * AD_BLOCK)
-    y[i] += beta * (xp ? x[i] - xp[i] : x[i]);
+// d = P e (trilinear; the clamped fine nodes get 0)
+__global__ __launch_bounds__(AD_BLOCK) void k_st_prolong(const double* __restrict__ e, double* __restrict__ d, int NXf,
+                                                         int NYf, int NZf, int NXc, int NYc) {
+  const long long nf = (long long)NXf * NYf * NZf;
+  for (long long v = (long long)blockIdx.x * AD_BLOCK + threadIdx.x; v < nf; v += (long long)gridDim.x * AD_BLOCK) {
+    const int i = (int)(v % NXf);
+    const long long t = v / NXf;
+    const int j = (int)(t % NYf), k = (int)(t / NYf);
+    const double w = ((i & 1) ? 0.5 : 1.0) * ((j & 1) ? 0.5 : 1.0) * ((k & 1) ? 0.5 : 1.0);
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      if (((c & 1) && !(i & 1)) || ((c & 2) && !(j & 1)) || ((c & 4) && !(k & 1))) continue;
+      const long long m = 3 * (((i + (c & 1)) >> 1) +
+                               (long long)NXc * (((j + ((c >> 1) & 1)) >> 1) + (long long)NYc * ((k + (c >> 2)) >> 1)));
+      s0 += w * e[m];
+      s1 += w * e[m + 1];
+      s2 += w * e[m + 2];
+    }
+    d[3 * v] = i ? s0 : 0.0;
+    d[3 * v + 1] = i ? s1 : 0.0;
+    d[3 * v + 2] = i ? s2 : 0.0;
+  }
 }
 
 // bc = P^T rf (full weighting, the transpose of the trilinear prolongation):
@@ -371,18 +398,35 @@ __global__ __launch_bounds__(AD_BLOCK) void k_st_restrict(const double* __restri
   }
 }
 
-// line search: alpha = (r . Kd) / (Kd . Kd), 0 when Kd = 0
-__global__ void k_st_alpha(double* __restrict__ st) {
-  st[ST_ALPHA] = st[ST_KK] > 0.0 ? st[ST_RKD] / st[ST_KK] : 0.0;
-}
-
-// t = r - alpha Kd
-__global__ __launch_bounds__(AD_BLOCK) void k_st_axmy(const double* __restrict__ r, const double* __restrict__ Kd,
-                                                      const double* __restrict__ st, double* __restrict__ t,
-                                                      long long n) {
-  const double a = st[ST_ALPHA];
-  for (long long i = (long long)blockIdx.x * AD_BLOCK + threadIdx.x; i < n; i += (long long)gridDim.x * AD_BLOCK)
-    t[i] = r[i] - a * Kd[i];
+// line search: alpha = (r . Kd) / (Kd . Kd), 0 when Kd = 0; per-block sums of
+// (r - alpha Kd)^2 (row 0) and r^2 (row 1)
+__global__ __launch_bounds__(AD_BLOCK) void k_st_line(const double* __restrict__ r, const double* __restrict__ Kd,
+                                                      double* __restrict__ st, long long n,
+                                                      double* __restrict__ part) {
+  __shared__ double red[2][AD_BLOCK / 64];
+  const double a = st[ST_KK] > 0.0 ? st[ST_RKD] / st[ST_KK] : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) st[ST_ALPHA] = a;
+  double tt = 0.0, rr = 0.0;
+  for (long long i = (long long)blockIdx.x * AD_BLOCK + threadIdx.x; i < n; i += (long long)gridDim.x * AD_BLOCK) {
+    const double ri = r[i], t = ri - a * Kd[i];
+    tt += t * t;
+    rr += ri * ri;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    tt += __shfl_xor(tt, off, 64);
+    rr += __shfl_xor(rr, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = tt;
+    red[1][threadIdx.x >> 6] = rr;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double s = 0.0;
+    for (int w = 0; w < AD_BLOCK / 64; ++w) s += red[threadIdx.x][w];
+    part[(long long)threadIdx.x * gridDim.x + blockIdx.x] = s;
+  }
 }
 
 // ratio = ||r - alpha Kd|| / ||r|| (1 when r = 0); the correction is kept,
@@ -418,6 +462,41 @@ struct Layout {
   bool stack = false;
   size_t oV = 0, oZ = 0, iV = 0, iZ = 0, wv = 0, f32 = 0, part = 0, small = 0, ist = 0;
   size_t s0 = 0, c1V = 0, c1Z = 0, c1x = 0, cist = 0, stk = 0, total = 0;
+  // Inner processes of up to TG_MAX_RESTART steps run on the batched
+  // delayed-CGS2 kernels (five launches per fine step instead of eleven); they
+  // need their own memory: offsets of a KrylovOne's arrays
+  struct Kry {
+    int q = 0;
+    size_t pool = 0, small = 0, part = 0, status = 0, list = 0, desc = 0;
+    void init(long long n, int steps, size_t& o) {
+      q = steps > 0 && steps <= TG_MAX_RESTART ? steps : 0;
+      if (!q) return;
+      const KrylovOne K = at(nullptr, n);
+      pool = o; o += (size_t)(2 * q + 2) * K.stride * sizeof(double);
+      small = o; o += al(K.sl.total * sizeof(double));
+      part = o; o += al((size_t)(2 * q + 3) * K.chunks * sizeof(double));
+      status = o; o += 256;
+      list = o; o += al((size_t)K.chunks * sizeof(int2));
+      desc = o; o += al(sizeof(ProbDesc));
+    }
+    KrylovOne at(char* base, long long n) const {
+      KrylovOne K;
+      K.q = q;
+      K.n = n;
+      K.chunks = (int)((n + TG_VCHUNK - 1) / TG_VCHUNK);
+      K.stride = (long long)K.chunks * TG_VCHUNK;
+      K.sl.init(q, q + 2);
+      if (base) {
+        K.pool = (double*)(base + pool);
+        K.small = (double*)(base + small);
+        K.part = (double*)(base + part);
+        K.status = (double*)(base + status);
+        K.list = (int2*)(base + list);
+        K.desc = (ProbDesc*)(base + desc);
+      }
+      return K;
+    }
+  } kf, kc;
   void init(const tg_grid* g, int restart, int inner, bool with_stack = false, int coarse = 0) {
     n = g->lv[0].n_dof;
     ld = ld_of(n);
@@ -432,8 +511,9 @@ struct Layout {
     size_t o = 0;
     oV = o; o += (size_t)(m > 0 ? m + 1 : 0) * vb;
     oZ = o; o += (size_t)m * vb;
-    iV = o; o += (size_t)(q > 0 ? q + 1 : 0) * vb;
-    iZ = o; o += (size_t)q * vb;
+    kf.init(n, q, o);
+    iV = o; o += (size_t)(q > 0 && !kf.q ? q + 1 : 0) * vb;
+    iZ = o; o += (size_t)(kf.q ? 0 : q) * vb;
     wv = o; o += 4 * vb;
     f32 = o; o += 2 * al((size_t)n * sizeof(float));
     part = o; o += al((size_t)nb * AD_MAXV * sizeof(double));
@@ -441,8 +521,9 @@ struct Layout {
     ist = o; o += inner_state_bytes(q);
     if (stack) {
       s0 = o; o += 6 * vb;
-      c1V = o; o += (size_t)(cs > 0 ? cs + 1 : 0) * vb1;
-      c1Z = o; o += (size_t)cs * vb1;
+      if (n1 > 0) kc.init(n1, cs, o);
+      c1V = o; o += (size_t)(cs > 0 && !kc.q ? cs + 1 : 0) * vb1;
+      c1Z = o; o += (size_t)(kc.q ? 0 : cs) * vb1;
       c1x = o; o += 3 * vb1;
       cist = o; o += inner_state_bytes(cs);
       stk = o; o += al((ST_N + TG_MAXLEV) * sizeof(double));
@@ -512,6 +593,18 @@ struct Ctx {
   double* C1(int i) const { return (double*)(base + L.c1x) + (long long)i * L.ld1; }
   double* stk() const { return (double*)(base + L.stk); }
   double* lams_d() const { return stk() + ST_N; }
+  // the inner processes on the batched kernels, bound at first use
+  KrylovOne kf() const { return L.kf.at(base, L.n); }
+  KrylovOne kc() const { return L.kc.at(base, L.n1); }
+  bool kry_bound = false;
+  int bind() {
+    if (kry_bound) return TG_OK;
+    kry_bound = true;
+    int rc = TG_OK;
+    if (L.kf.q) rc = krylov_bind(kf(), s);
+    if (!rc && L.kc.q) rc = krylov_bind(kc(), s);
+    return rc;
+  }
   bool flag_pending = false;   // a decision of M waits in isc()[IS_ACC]
   std::vector<int> accepted;
   // the full stack: options, lambda~ per level, one log entry per application
@@ -801,6 +894,16 @@ int inner_gmres(Ctx& c, const Inner& S, const double* rhs, double* w, double* d,
   return TG_OK;
 }
 
+// y = b - K x on every free DOF of the finest level, 0 on the clamped ones
+int k_resid64(Ctx& c, const double* x, const double* b, double* y) {
+  // (a one-level grid has no smoothing tiles: the operator's list is the same set)
+  const DevList& dl = c.g->self->fine;
+  const int rc = launch_fine<double>(c.g->self, dl, 0, LV_RESID, -1, x, -1, b, -1, y, 0.0, c.s);
+  if (rc) return rc;
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
+
 // The fine-level correction of z (Tab. solver-config): with s = v - K z, q
 // inner GMRES steps on K d = s preconditioned by the node-block Jacobi
 // operator; z += d iff ||s - K d|| < ||s||.  The decision is left in
@@ -816,13 +919,25 @@ int fine_correction(Ctx& c, const double* v, double* z) {
   double* t = c.W(2);
   double* d = c.W(3);
   double* sc = c.isc();
-  if ((rc = applyK(c, z, t))) return rc;
-  if ((rc = axpby(c, 1.0, v, -1.0, t, s))) return rc;
-  rc = inner_gmres(c, c.fine_inner(), s, c.W(0), d, [&c](const double* x, double* y) { return applyK(c, x, y); },
-                   [&c](const double* x, double* y) { return jacobi(c, x, y); });
-  if (rc) return rc;
-  if ((rc = applyK(c, d, t))) return rc;
-  if ((rc = axpby(c, 1.0, s, -1.0, t, t))) return rc;
+  Batch* B = c.g->self;
+  if ((rc = batch_set_active(B, {0}, c.s))) return rc;
+  if ((rc = k_resid64(c, z, v, s))) return rc;
+  if (c.L.kf.q) {
+    const KrylovOne K = c.kf();
+    if ((rc = c.bind())) return rc;
+    if ((rc = krylov_start(K, s, sc + IS_R0SQ, c.s))) return rc;
+    for (int j = 0; j < K.q; ++j) {
+      // z_j = D^-1 v_j while w = K z_j is formed
+      if ((rc = level_apply_jacobi64(B, K.V(j), K.scale(), K.Z(j), K.W(), c.s))) return rc;
+      if ((rc = krylov_step(K, j, c.s))) return rc;
+    }
+    if ((rc = krylov_finish(K, d, c.s))) return rc;
+  } else {
+    rc = inner_gmres(c, c.fine_inner(), s, c.W(0), d, [&c](const double* x, double* y) { return applyK(c, x, y); },
+                     [&c](const double* x, double* y) { return jacobi(c, x, y); });
+    if (rc) return rc;
+  }
+  if ((rc = k_resid64(c, d, s, t))) return rc;
   if ((rc = dots(c, t, 1, t, nullptr, 0, sc + IS_R1SQ))) return rc;
   k_ad_accept<<<nblk(c.L.n), AD_BLOCK, 0, c.s>>>(z, d, sc, c.L.n);
   TG_HIP(hipGetLastError());
@@ -879,40 +994,31 @@ void cheb_coefs(double lam, int deg, double lo, double hi, double* om, double* b
   }
 }
 
-int st_jacobi(Ctx& c, int l, const double* b, double* x, double om) {
+int st_jacobi(Ctx& c, int l, const double* b, double* x, double om, const double* scale = nullptr,
+              double* bcopy = nullptr) {
   const long long nn = c.g->lv[l].n_nodes;
-  k_st_jacobi<<<nblk(nn), AD_BLOCK, 0, c.s>>>(c.g->desc.lv[l].Dinv64, b, x, om, nn, c.g->desc.lv[l].NX);
+  k_st_jacobi<<<nblk(nn), AD_BLOCK, 0, c.s>>>(c.g->desc.lv[l].Dinv64, b, scale, x, bcopy, om, nn, c.g->desc.lv[l].NX);
   TG_HIP(hipGetLastError());
   return TG_OK;
 }
 
-constexpr int ST_MAX_DEGREE = 16;
+constexpr int ST_MAX_DEGREE = 16;   // (as the one-launch bottom's coefficient arrays)
 
-// Chebyshev iteration of degree deg at level l on K_l x = b from x0 (NULL:
-// from zero).  The iterates rotate through rot[0..2] (distinct from b; x0 may
-// be one of them); the last goes to out if out is non-NULL (distinct from b,
-// x0 and rot), else it stays in rot.  *res = the result.
-int cheb(Ctx& c, int l, const double* b, const double* x0, double* out, int deg, double* const* rot,
-         const double** res) {
+// Steps k0.. of the Chebyshev iteration of degree deg at level l on K_l x = b
+// with x_k0 = xc and x_{k0-1} = xp.  The iterates rotate through rot[0..2]
+// (distinct from b; xc and xp may be among them); the last goes to out if out
+// is non-NULL (distinct from b, xc, xp and rot).  *res = the result.
+int cheb_steps(Ctx& c, int l, const double* b, const double* xc, const double* xp, int k0, int deg, const double* om,
+               const double* be, double* out, double* const* rot, const double** res) {
   int rc;
-  double om[ST_MAX_DEGREE], be[ST_MAX_DEGREE];
-  cheb_coefs(c.lam[l], deg, c.so.lo, c.so.hi, om, be);
-  const long long n = lvl_n(c, l);
-  const double* xc = x0;   // x_k
-  const double* xp = x0;   // x_{k-1}
-  for (int k = 0; k < deg; ++k) {
+  Batch* B = c.g->self;
+  for (int k = k0; k < deg; ++k) {
     double* dst = (k == deg - 1) ? out : nullptr;
     for (int i = 0; i < 3 && !dst; ++i)
       if (rot[i] != xc && rot[i] != xp) dst = rot[i];
-    if (!xc) {
-      if ((rc = st_jacobi(c, l, b, dst, om[0]))) return rc;   // x_1 = omega_0 D^-1 b
-    } else {
-      if ((rc = level_op64(c.g->self, l, LV_SMOOTH, xc, b, dst, om[k], c.s))) return rc;
-      if (be[k] != 0.0) {
-        k_st_cheb_fix<<<nblk(n), AD_BLOCK, 0, c.s>>>(dst, xc, xp, be[k], n);
-        TG_HIP(hipGetLastError());
-      }
-    }
+    if (be[k] != 0.0) rc = level_cheb_step64(B, l, xc, xp, b, om[k], be[k], dst, c.s);
+    else rc = level_op64(B, l, LV_SMOOTH, xc, b, dst, om[k], c.s);
+    if (rc) return rc;
     xp = xc;
     xc = dst;
   }
@@ -920,13 +1026,48 @@ int cheb(Ctx& c, int l, const double* b, const double* x0, double* out, int deg,
   return TG_OK;
 }
 
-// The V-cycle with Chebyshev smoothing from level l >= 1 on K_l x = b (b an
-// external vector or level l's slot C_B): result to out if non-NULL (distinct
-// from b and level l's other slots), else left in one of level l's slots
-// C_XA, C_XB, C_R; *res = the result.
-int cheb_vcycle(Ctx& c, int l, const double* b, double* out, const double** res) {
+// Chebyshev iteration of degree deg at level l on K_l x = *scale b from zero
+// (scale NULL: 1), the first two steps in one launch; with a scale, bcopy
+// receives *scale b, which the steps after them read.
+int cheb_zero(Ctx& c, int l, const double* b, const double* scale, double* bcopy, double* out, int deg,
+              double* const* rot, const double** res) {
+  int rc;
+  double om[ST_MAX_DEGREE], be[ST_MAX_DEGREE];
+  cheb_coefs(c.lam[l], deg, c.so.lo, c.so.hi, om, be);
+  double* x = (deg <= 2 && out) ? out : rot[0];
+  *res = x;
+  if (deg == 1) return st_jacobi(c, l, b, x, om[0], scale, scale ? bcopy : nullptr);   // x_1 = omega_0 D^-1 b
+  if (deg == 2) return level_cheb_first64(c.g->self, l, b, scale, om[0], om[1], be[1], x, scale ? bcopy : nullptr, c.s);
+  // more steps need x_1 itself
+  if ((rc = st_jacobi(c, l, b, x, om[0], scale, scale ? bcopy : nullptr))) return rc;
+  const double* bb = scale ? bcopy : b;
+  double* x2 = rot[1];
+  if ((rc = level_cheb_first64(c.g->self, l, bb, nullptr, om[0], om[1], be[1], x2, nullptr, c.s))) return rc;
+  return cheb_steps(c, l, bb, x2, x, 2, deg, om, be, out, rot, res);
+}
+// ... from x0 (one of rot, or any vector distinct from b and out)
+int cheb_from(Ctx& c, int l, const double* b, const double* x0, double* out, int deg, double* const* rot,
+              const double** res) {
+  double om[ST_MAX_DEGREE], be[ST_MAX_DEGREE];
+  cheb_coefs(c.lam[l], deg, c.so.lo, c.so.hi, om, be);
+  return cheb_steps(c, l, b, x0, x0, 0, deg, om, be, out, rot, res);
+}
+
+// The V-cycle with Chebyshev smoothing from level l >= 1 on K_l x = *scale b (b
+// an external vector or level l's slot C_B; scale NULL: 1): result to out if
+// non-NULL (distinct from b and level l's other slots), else left in one of
+// level l's slots C_XA, C_XB, C_R; *res = the result.
+int cheb_vcycle(Ctx& c, int l, const double* b, const double* scale, double* out, const double** res) {
   int rc;
   Batch* B = c.g->self;
+  if (B->vb[1].n && l == B->host_desc[0].vb_lb64) {
+    // the levels that fit one workgroup's LDS, in one launch
+    double om[TG_MAXLEV][ST_MAX_DEGREE] = {}, be[TG_MAXLEV][ST_MAX_DEGREE] = {};
+    const int deg = std::max(c.so.nu_pre, c.so.nu_post);
+    for (int q = l; q < c.g->nlev - 1; ++q) cheb_coefs(c.lam[q], deg, c.so.lo, c.so.hi, om[q], be[q]);
+    *res = out ? out : pool64(c, l, C_XA);
+    return level_vbottom_cheb64(B, om, be, b, scale, out, c.so.nu_pre, c.so.nu_post, c.s);
+  }
   if (l == c.g->nlev - 1) {
     double* y = out ? out : pool64(c, l, C_XA);
     if ((rc = level_coarse64(B, l, b, y, c.s))) return rc;
@@ -936,12 +1077,24 @@ int cheb_vcycle(Ctx& c, int l, const double* b, double* out, const double** res)
   double* rot[3] = {pool64(c, l, C_XA), pool64(c, l, C_XB), pool64(c, l, C_R)};
   const double* x;
   const double* e;
-  if ((rc = cheb(c, l, b, nullptr, nullptr, c.so.nu_pre, rot, &x))) return rc;
+  if ((rc = cheb_zero(c, l, b, scale, pool64(c, l, C_B), nullptr, c.so.nu_pre, rot, &x))) return rc;
+  if (scale) b = pool64(c, l, C_B);
   // the residual restricted straight into level l + 1's right-hand side
   if ((rc = level_restrict64(B, l, x, b, C_B, c.s))) return rc;
-  if ((rc = cheb_vcycle(c, l + 1, pool64(c, l + 1, C_B), nullptr, &e))) return rc;
-  if ((rc = level_prolong64(B, l, e, const_cast<double*>(x), c.s))) return rc;
-  return cheb(c, l, b, x, out, c.so.nu_post, rot, res);
+  if ((rc = cheb_vcycle(c, l + 1, pool64(c, l + 1, C_B), nullptr, nullptr, &e))) return rc;
+  if (!fine_prolongs(B, l)) {
+    if ((rc = level_prolong64(B, l, e, const_cast<double*>(x), c.s))) return rc;
+    return cheb_from(c, l, b, x, out, c.so.nu_post, rot, res);
+  }
+  // the first post-step forms x + P e itself, and keeps it for the second
+  double om[ST_MAX_DEGREE], be[ST_MAX_DEGREE];
+  cheb_coefs(c.lam[l], c.so.nu_post, c.so.lo, c.so.hi, om, be);
+  double* o[2];
+  for (int i = 0, q = 0; i < 3; ++i)
+    if (rot[i] != x && q < 2) o[q++] = rot[i];
+  double* y = c.so.nu_post == 1 && out ? out : o[0];
+  if ((rc = level_cheb_prolong64(B, l, x, e, b, om[0], y, c.so.nu_post > 1 ? o[1] : nullptr, c.s))) return rc;
+  return cheb_steps(c, l, b, y, o[1], 1, c.so.nu_post, om, be, out, rot, res);
 }
 
 // lambda~ of every level above the coarsest into c.lam (synchronizes)
@@ -989,10 +1142,13 @@ int stack_apply(Ctx& c, const double* v, double* z) {
   double* st = c.stk();
   const double* x;
   const double* xo;
-  if ((rc = cheb(c, 0, v, nullptr, nullptr, c.so.nu_pre, rot, &x))) return rc;
+  if ((rc = c.bind())) return rc;
+  if ((rc = cheb_zero(c, 0, v, nullptr, nullptr, nullptr, c.so.nu_pre, rot, &x))) return rc;
   if ((rc = level_op64(B, 0, LV_RESID, x, v, r, 0.0, c.s))) return rc;
   // coarse right-hand side b1 = P^T r and the coarse correction e
-  double* b1 = c.C1(0);
+  const bool kry = c.g->nlev > 2 && c.L.cs > 0 && c.L.kc.q;
+  const KrylovOne K = c.kc();
+  double* b1 = kry ? K.V(0) : c.C1(0);
   double* e = c.C1(1);
   const LevelDesc& L0 = c.g->desc.lv[0];
   const LevelDesc& L1 = c.g->desc.lv[1];
@@ -1001,29 +1157,36 @@ int stack_apply(Ctx& c, const double* v, double* z) {
   if (c.g->nlev == 2) {
     if ((rc = level_coarse64(B, 1, b1, e, c.s))) return rc;
   } else if (c.L.cs == 0) {
-    if ((rc = cheb_vcycle(c, 1, b1, e, &xo))) return rc;
+    if ((rc = cheb_vcycle(c, 1, b1, nullptr, e, &xo))) return rc;
+  } else if (kry) {
+    if ((rc = krylov_start(K, b1, st + ST_PW, c.s))) return rc;
+    for (int j = 0; j < K.q; ++j) {
+      if ((rc = cheb_vcycle(c, 1, K.V(j), K.scale(), K.Z(j), &xo))) return rc;
+      if ((rc = level_op64(B, 1, LV_APPLY, K.Z(j), nullptr, K.W(), 0.0, c.s))) return rc;
+      if ((rc = krylov_step(K, j, c.s))) return rc;
+    }
+    if ((rc = krylov_finish(K, e, c.s))) return rc;
   } else {
     auto A1 = [&c, B](const double* a, double* y) { return level_op64(B, 1, LV_APPLY, a, nullptr, y, 0.0, c.s); };
     auto M1 = [&c](const double* a, double* y) {
       const double* res;
-      return cheb_vcycle(c, 1, a, y, &res);
+      return cheb_vcycle(c, 1, a, nullptr, y, &res);
     };
     if ((rc = inner_gmres(c, c.coarse_inner(), b1, c.C1(2), e, A1, M1))) return rc;
   }
   // d = P e, K d, and the line search on the fine residual
-  TG_HIP(hipMemsetAsync(dc, 0, sizeof(double) * n, c.s));
-  if ((rc = level_prolong64(B, 0, e, dc, c.s))) return rc;
+  k_st_prolong<<<nblk(c.g->lv[0].n_nodes), AD_BLOCK, 0, c.s>>>(e, dc, L0.NX, L0.NY, L0.NZ, L1.NX, L1.NY);
+  TG_HIP(hipGetLastError());
   if ((rc = level_op64(B, 0, LV_APPLY, dc, nullptr, Kd, 0.0, c.s))) return rc;
   if ((rc = dots(c, r, 1, Kd, nullptr, 0, st + ST_RKD, st + ST_KK))) return rc;
-  k_st_alpha<<<1, 1, 0, c.s>>>(st);
+  const int nbd = nblk_dots(n);
+  k_st_line<<<nbd, AD_BLOCK, 0, c.s>>>(r, Kd, st, n, c.part());
   TG_HIP(hipGetLastError());
-  k_st_axmy<<<nb, AD_BLOCK, 0, c.s>>>(r, Kd, st, c.W(2), n);
+  k_ad_sum<<<2, 64, 0, c.s>>>(c.part(), nbd, 1, st + ST_TT, nullptr, 0, st + ST_RR);
   TG_HIP(hipGetLastError());
-  if ((rc = dots(c, c.W(2), 1, c.W(2), nullptr, 0, st + ST_TT))) return rc;
-  if ((rc = dots(c, r, 1, r, nullptr, 0, st + ST_RR))) return rc;
   k_st_accept<<<nb, AD_BLOCK, 0, c.s>>>(st, c.so.theta, const_cast<double*>(x), dc, n);
   TG_HIP(hipGetLastError());
-  if ((rc = cheb(c, 0, v, x, z, c.so.nu_post, rot, &xo))) return rc;
+  if ((rc = cheb_from(c, 0, v, x, z, c.so.nu_post, rot, &xo))) return rc;
   return fine_correction(c, v, z);
 }
 

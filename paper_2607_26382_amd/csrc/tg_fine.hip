@@ -34,7 +34,8 @@ __host__ __device__ __forceinline__ float mad_(float a, float b, float c) { retu
 __host__ __device__ __forceinline__ double mad_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 enum { FOP_APPLY = 0, FOP_RESID = 1, FOP_SMOOTH = 2, FOP_RESTRICT = 3, FOP_SMOOTH1 = 4, FOP_SMOOTH1E = 5,
-       FOP_SMOOTHP = 6 };
+       FOP_SMOOTHP = 6, FOP_APPLYJ = 7, FOP_CHEB1 = 8, FOP_SMOOTHC = 9,
+       FOP_SMOOTHPX = 10 };
 // FOP_SMOOTH1 (level 0): the first two sweeps from x = 0 in one pass.  The
 // right-hand side is read from an FP64 slot (sb), times the per-problem scale
 // small[sx] when sx >= 0; every staged node gets x = w D^-1 b on the fly (the
@@ -44,6 +45,18 @@ enum { FOP_APPLY = 0, FOP_RESID = 1, FOP_SMOOTH = 2, FOP_RESTRICT = 3, FOP_SMOOT
 // FOP_SMOOTHP: a smoothing sweep of x + P e, e the next level's vector in slot
 // sy2: the tile's coarse nodes are held in LDS and every staged node is
 // corrected there, in place of a prolongation pass over x.
+// For host-stepped cycles (FP64, external vectors; fx.scale: a factor of b on
+// the device, 1 if null):
+// FOP_APPLYJ: y = K x with x = w D^-1 (scale b) formed while staging; x to fx.xo.
+// FOP_CHEB1: the first two Chebyshev steps from zero, x = w D^-1 (scale b) and
+// y = x + om2 D^-1 (scale b - K x) + beta x; scale b to fx.xo if given.
+// FOP_SMOOTHC: y = x + w D^-1 (b - K x) + beta (x - xp).
+// FOP_SMOOTHPX: FOP_SMOOTHP with e from fx.e; x + P e also to fx.xo if given.
+// A host-stepped cycle is a chain of launches of 4-15 us, most of it the chain
+// of loads of each, so what counts is their number: with these three forms, the
+// prolongation above and the batched Gram-Schmidt kernels one application of
+// the adaptive stack (64x32x32, 20 fine and 10 coarse steps) makes some 310 launches
+// in place of 735, 3894 -> 2580 us.
 
 // Tiling of the residual sweep fused with the restriction (OP = FOP_RESTRICT):
 // a tile owns 7 x 7 coarse node columns and m coarse node layers, and computes
@@ -361,6 +374,30 @@ __host__ __device__ __forceinline__ int fz_tiles(int NX, int NY, int NZ, int zc)
   return ((NX + FZ_OUT - 1) / FZ_OUT) * ((NY + FZ_OUT - 1) / FZ_OUT) * ((NZ + zc - 1) / zc);
 }
 
+// Extra operands of the ops that name them (the others take none: 48 bytes more
+// of kernel arguments cost a launch some 0.3 us).
+template <class T>
+struct FzX {
+  const double* scale;
+  const T* e;
+  T* xo;
+  const T* xp;
+  T om2, beta;
+};
+struct FzNone {};
+// (a member type: a kernel's signature must not spell out an enumerator of the
+// unnamed enum, whose mangled number differs between the host and device passes)
+template <class T, int OP>
+struct FzArgOf {
+  typedef std::conditional_t<(OP >= FOP_APPLYJ), FzX<T>, FzNone> type;
+};
+template <class T, int OP>
+using FzArg = typename FzArgOf<T, OP>::type;
+template <class T>
+__device__ inline FzX<T> fz_x(const FzX<T>& a) { return a; }
+template <class T>
+__device__ inline FzX<T> fz_x(const FzNone&) { return {}; }
+
 // KIND 0: fine level, element = E_e Ke; KIND 1: level 1, matrix-free Galerkin
 // (moment form); KIND 2 / 3: fine level with the BF16 matrix-core contraction
 // (3: split BF16); KIND 4: level l >= 2, stored mode-basis Galerkin elements.
@@ -369,7 +406,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
                                                  const int2* __restrict__ work, int l, int sx,
                                                  const void* ex_, int sb, const void* eb_, int sy,
                                                  void* ey_, int sy2, T omega, ModeCoef<T> mc,
-                                                 int vbskip) {
+                                                 int vbskip, FzArg<T, OP> fxa) {
   // Single buffers suffice: every read of a layer's values happens between the
   // two barriers of its step, every write of the next layer after them.
   constexpr bool MF = (KIND == 2 || KIND == 3);   // matrix-core forms
@@ -393,7 +430,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
   // FOP_SMOOTHP: the tile's coarse nodes, 3 components each, layer by layer
   extern __shared__ __align__(16) unsigned char fz_smem[];
   T* sc = (T*)fz_smem;
-  constexpr bool SP = (OP == FOP_SMOOTHP);
+  constexpr bool SP = (OP == FOP_SMOOTHP || OP == FOP_SMOOTHPX);
   MfmaA mfA;
   const int2 wi = work[xcd_tile(blockIdx.x, gridDim.x)];
   const ProbDesc& P = probs[wi.x];
@@ -446,8 +483,12 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
     T a0, a1, a2, e0, e1, e2;
     T b0, b1, b2;              // FOP_SMOOTH1: b at the own node
   };
-  constexpr bool S1 = (OP == FOP_SMOOTH1 || OP == FOP_SMOOTH1E);
-  const double in_scale = (S1 && sx >= 0) ? P.small[sx] : 1.0;
+  const FzX<T> fx = fz_x<T>(fxa);
+  constexpr bool XB = (OP == FOP_APPLYJ || OP == FOP_CHEB1);   // b external, scaled by *fx.scale
+  constexpr bool S1 = (OP == FOP_SMOOTH1 || OP == FOP_SMOOTH1E || XB);
+  constexpr bool AP = (OP == FOP_APPLY || OP == FOP_APPLYJ);   // the output is K x
+  constexpr bool DO = (OP == FOP_SMOOTH || SP || OP == FOP_SMOOTHC || (S1 && !AP));   // D^-1 at the output
+  const double in_scale = XB ? (fx.scale ? *fx.scale : 1.0) : (S1 && sx >= 0) ? P.small[sx] : 1.0;
   // FOP_SMOOTH1: b at node (column base, layer k) from the FP64 slot, scaled,
   // and the first sweep x = w D^-1 b there
   auto first_sweep = [&](long long base, int k, T& x0, T& x1, T& x2, T& c0, T& c1, T& c2) {
@@ -456,6 +497,11 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
       c0 = bp[0];
       c1 = bp[1];
       c2 = bp[2];
+    } else if constexpr (XB) {
+      const T TG_GLOBAL* bp = gp((const T*)eb_) + base + lstride * k;
+      c0 = bp[0] * T(in_scale);
+      c1 = bp[1] * T(in_scale);
+      c2 = bp[2] * T(in_scale);
     } else {
       const double TG_GLOBAL* bp = gp(P.lv[0].vec64 + (long long)sb * L.stride) + base + lstride * k;
       c0 = T(bp[0] * in_scale);
@@ -524,7 +570,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
   const int cx0 = (x0 - 1) >> 1, cy0 = (y0 - 1) >> 1, cz0 = (z0 - 1) >> 1;
   if constexpr (SP) {
     const LevelDesc& Lc = P.lv[l + 1];
-    const auto* e = gp(fvec<T>(Lc, sy2, nullptr));
+    const auto* e = gp(OP == FOP_SMOOTHPX ? fx.e : fvec<T>(Lc, sy2, nullptr));
     const int nl = ((zend + 1) >> 1) - cz0 + 1;
     for (int q = threadIdx.x; q < nl * FZ_C * FZ_C * 3; q += 256) {
       const int c = q % 3, m = q / 3, I = m % FZ_C + cx0, t = m / FZ_C, J = t % FZ_C + cy0, K = t / FZ_C + cz0;
@@ -648,13 +694,20 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
     T D[9];
     const bool out_now = owner && own_col && k >= z0 && k >= 0;
     const long long n = ni + (long long)NX * (nj + (long long)NY * k);
+    T xp[3] = {T(0), T(0), T(0)};
     if (S1) {
       rb0 = bo0; rb1 = bo1; rb2 = bo2;
-    } else if (OP != FOP_APPLY && out_now) {
+    } else if (!AP && out_now) {
       const auto* bb = gp(fvec<T>(L, sb, eb_)) + 3 * n;
       rb0 = bb[0]; rb1 = bb[1]; rb2 = bb[2];
     }
-    if ((OP == FOP_SMOOTH || SP || S1) && out_now) {
+    if constexpr (OP == FOP_SMOOTHC) {
+      if (out_now) {
+        const auto* xq = gp(fx.xp) + 3 * n;
+        xp[0] = xq[0]; xp[1] = xq[1]; xp[2] = xq[2];
+      }
+    }
+    if (DO && out_now) {
       const auto* Dp = gp(fD<T>(L)) + 9 * n;
 #pragma unroll
       for (int q = 0; q < 9; ++q) D[q] = Dp[q];
@@ -772,7 +825,14 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
         for (int q = 0; q < 3; ++q) rl[q][ty][tx] = out_now ? (q == 0 ? rb0 : q == 1 ? rb1 : rb2) - a[q] : T(0);
       } else {
       auto* y = gp((sy < 0 ? (TY*)ey_ : fpool<TY>(L) + (long long)sy * L.stride)) + 3 * n;
-      if constexpr (S1) {
+      if constexpr (XB || OP == FOP_SMOOTHPX) {
+        if (fx.xo) {
+          auto* xo = gp(fx.xo) + 3 * n;
+          xo[0] = OP == FOP_CHEB1 ? rb0 : own0;
+          xo[1] = OP == FOP_CHEB1 ? rb1 : own1;
+          xo[2] = OP == FOP_CHEB1 ? rb2 : own2;
+        }
+      } else if constexpr (S1) {
         // the FP32 copy of b for the later sweeps (zero at clamped nodes)
         auto* bt = gp(fpool<T>(L) + (long long)sy2 * L.stride) + 3 * n;
         bt[0] = rb0;
@@ -781,7 +841,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
       }
       if (ni == 0) {
         y[0] = y[1] = y[2] = TY(0);
-      } else if (OP == FOP_APPLY) {
+      } else if (AP) {
         y[0] = TY(a[0]);
         y[1] = TY(a[1]);
         y[2] = TY(a[2]);
@@ -791,6 +851,14 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
           y[0] = TY(r0);
           y[1] = TY(r1);
           y[2] = TY(r2);
+        } else if (OP == FOP_CHEB1 || OP == FOP_SMOOTHC) {
+          const T w = OP == FOP_CHEB1 ? fx.om2 : omega;
+          const T y0 = mad_(w, mad_(D[2], r2, mad_(D[1], r1, D[0] * r0)), own0);
+          const T y1 = mad_(w, mad_(D[5], r2, mad_(D[4], r1, D[3] * r0)), own1);
+          const T y2 = mad_(w, mad_(D[8], r2, mad_(D[7], r1, D[6] * r0)), own2);
+          y[0] = TY(mad_(fx.beta, own0 - xp[0], y0));
+          y[1] = TY(mad_(fx.beta, own1 - xp[1], y1));
+          y[2] = TY(mad_(fx.beta, own2 - xp[2], y2));
         } else {
           y[0] = TY(mad_(omega, mad_(D[2], r2, mad_(D[1], r1, D[0] * r0)), own0));
           y[1] = TY(mad_(omega, mad_(D[5], r2, mad_(D[4], r1, D[3] * r0)), own1));
@@ -1096,7 +1164,7 @@ int launch_fine(const Batch* b, const DevList& dl, int l, int op, int sx, const 
   // (dynamic LDS: the coarse nodes of a prolonging sweep)
   const size_t dyn = op == FOP_SMOOTHP ? fz_coarse_bytes(b, l, sizeof(T)) : 0;
 #define TG_ZMOP(OPV, KV) \
-  k_fine_zm<T, OPV, KV><<<dl.n, 256, dyn, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip)
+  k_fine_zm<T, OPV, KV><<<dl.n, 256, dyn, s>>>(desc, dl.ptr, l, sx, ex, sb, eb, sy, ey, sy2, om, mc, vbskip, {})
 #define TG_ZM(KV)                                        \
   do {                                                   \
     if (op == FOP_APPLY) TG_ZMOP(FOP_APPLY, KV);         \
@@ -1133,7 +1201,7 @@ int launch_fine_mfma(const Batch* b, const DevList& dl, int op, bool split, int 
   const float om = float(omega);
   const size_t dyn = op == FOP_SMOOTHP ? fz_coarse_bytes(b, 0, sizeof(float)) : 0;
 #define TG_MF(OPV, K, TYV) \
-  k_fine_zm<float, OPV, K, TYV><<<dl.n, 256, dyn, s>>>(desc, dl.ptr, 0, sx, ex, sb, eb, sy, ey, sy2, om, mc, 0)
+  k_fine_zm<float, OPV, K, TYV><<<dl.n, 256, dyn, s>>>(desc, dl.ptr, 0, sx, ex, sb, eb, sy, ey, sy2, om, mc, 0, {})
   if (out64) {
     if (split) TG_MF(FOP_SMOOTH, 3, double); else TG_MF(FOP_SMOOTH, 2, double);
   } else if (op == FOP_APPLY) {
@@ -1162,11 +1230,55 @@ int launch_fine_smooth_out64(const Batch* b, const DevList& dl, int sx, int sb, 
   if (!dl.n) return TG_OK;
   const ModeCoef<float> mc = mcoef<float>(b->grids[0]);
   k_fine_zm<float, FOP_SMOOTH, 0, double><<<dl.n, 256, 0, s>>>(b->desc_d, dl.ptr, 0, sx, nullptr, sb, nullptr,
-                                                               sy, nullptr, -1, float(omega), mc, 0);
+                                                               sy, nullptr, -1, float(omega), mc, 0, {});
   return TG_OK;
 }
 template int launch_fine<float>(const Batch*, const DevList&, int, int, int, const void*, int, const void*,
                                 int, void*, double, hipStream_t, int, int);
+
+// Level primitives of host-stepped cycles (FP64, external vectors of level l).
+template <int OP>
+static void launch_x64(const Batch* b, const DevList& dl, int l, const double* x, const double* bb, double* y,
+                       double omega, const FzX<double>& fx, size_t dyn, hipStream_t s) {
+  if (!dl.n) return;
+  const ModeCoef<double> mc = mcoef<double>(b->grids[0]);
+#define TG_X64(KV) \
+  k_fine_zm<double, OP, KV><<<dl.n, 256, dyn, s>>>(b->desc_d, dl.ptr, l, -1, x, -1, bb, -1, y, -1, omega, mc, 0, fx)
+  if (l == 0) TG_X64(0);
+  else if (l <= TG_MF_LEVELS) TG_X64(1);
+  else TG_X64(4);
+#undef TG_X64
+}
+// z = D^-1 (*scale bb), y = K z (finest level)
+int level_apply_jacobi64(const Batch* b, const double* bb, const double* scale, double* z, double* y, hipStream_t s) {
+  launch_x64<FOP_APPLYJ>(b, b->fine, 0, nullptr, bb, y, 1.0, {scale, nullptr, z, nullptr, 0.0, 0.0}, 0, s);
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
+// the first two Chebyshev steps from zero on K y = *scale bb; bcopy (may be
+// NULL) receives the scaled right-hand side
+int level_cheb_first64(const Batch* b, int l, const double* bb, const double* scale, double om0, double om1,
+                       double be1, double* y, double* bcopy, hipStream_t s) {
+  launch_x64<FOP_CHEB1>(b, b->zm_s[l], l, nullptr, bb, y, om0, {scale, nullptr, bcopy, nullptr, om1, be1}, 0, s);
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
+// y = x + om D^-1 (bb - K x) + be (x - xp)
+int level_cheb_step64(const Batch* b, int l, const double* x, const double* xp, const double* bb, double om, double be,
+                      double* y, hipStream_t s) {
+  launch_x64<FOP_SMOOTHC>(b, b->zm_s[l], l, x, bb, y, om, {nullptr, nullptr, nullptr, xp, 0.0, be}, 0, s);
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
+// y = x' + om D^-1 (bb - K x') with x' = x + P e, which xo receives (levels
+// where fine_prolongs)
+int level_cheb_prolong64(const Batch* b, int l, const double* x, const double* e, const double* bb, double om,
+                         double* y, double* xo, hipStream_t s) {
+  launch_x64<FOP_SMOOTHPX>(b, b->zm_s[l], l, x, bb, y, om, {nullptr, e, xo, nullptr, 0.0, 0.0},
+                          fz_coarse_bytes(b, l, sizeof(double)), s);
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
 
 // ---------------------------------------------------------------------------
 // The bottom of the V-cycle in one launch.  From a level lb >= 2 down, every
@@ -1318,9 +1430,10 @@ __device__ __forceinline__ void vb_gather(const VbLev<T>& V, const T* eb, int i,
 // One damped node-block Jacobi sweep x <- x + w D^-1 (b - K x) (RESID =
 // false; after the element pass a node's update reads only its own x, so x
 // is updated in place), or r = b - K x into rbuf (RESID = true); clamped
-// nodes 0.
-template <class T, bool RESID, bool L1>
-__device__ void vb_sweep(const ProbDesc& P, int l, const VbLev<T>& V, T* eb, T* rbuf, T omega) {
+// nodes 0.  CH: a Chebyshev step, x <- x + w D^-1 (b - K x) + beta (x - xp)
+// with the previous iterate xp in rbuf, which takes x (beta = 0: xp unused).
+template <class T, bool RESID, bool L1, bool CH = false>
+__device__ void vb_sweep(const ProbDesc& P, int l, const VbLev<T>& V, T* eb, T* rbuf, T omega, T beta = T(0)) {
   const LevelDesc& L = P.lv[l];
   vb_elements<T, L1>(P, l, L, V, eb);
   __syncthreads();
@@ -1344,6 +1457,14 @@ __device__ void vb_sweep(const ProbDesc& P, int l, const VbLev<T>& V, T* eb, T* 
 #pragma unroll
       for (int c = 0; c < 3; ++c)
         xn[c] = mad_(omega, mad_(D[3 * c + 2], r2, mad_(D[3 * c + 1], r1, D[3 * c] * r0)), V.x[3 * n + c]);
+      if constexpr (CH) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const T x = V.x[3 * n + c];
+          if (beta != T(0)) xn[c] = mad_(beta, x - rbuf[3 * n + c], xn[c]);
+          rbuf[3 * n + c] = x;
+        }
+      }
 #pragma unroll
       for (int c = 0; c < 3; ++c) dst[3 * n + c] = xn[c];
     }
@@ -1508,6 +1629,75 @@ __global__ __launch_bounds__((VbThreads<T, L1>::N)) void k_vbottom(const ProbDes
   for (int q = threadIdx.x; q < 3 * Vb.nn; q += (int)blockDim.x) yg[q] = Vb.x[q];
 }
 
+// The same bottom with Chebyshev smoothing (FP64, host-stepped cycles): the
+// level-lb right-hand side is *scale eb (scale NULL: 1; eb NULL: slot C_B), the
+// result goes to ey (NULL: slot C_XA).  A workgroup steps the levels that it
+// holds in LDS faster than the chip does by launches: 26 us in place of five
+// launches for a 16x8x8 level above the coarsest (one application of the stack,
+// 64x32x32 with 10 coarse steps: 2580 -> 2352 us).
+struct VbCheb {
+  double om[TG_MAXLEV][16], be[TG_MAXLEV][16];
+};
+template <bool L1>
+__global__ __launch_bounds__((VbThreads<double, L1>::N)) void k_vbottom_cheb(const ProbDesc* __restrict__ probs,
+                                                                             const int2* __restrict__ work, VbCheb ch,
+                                                                             const double* eb_, const double* scale,
+                                                                             double* ey_, int nu_pre, int nu_post) {
+  typedef double T;
+  extern __shared__ __align__(16) unsigned char vb_smem[];
+  const ProbDesc& P = probs[work[blockIdx.x].x];
+  const int lb = P.vb_lb64, Lc = P.nlev - 1;
+  T* eb = (T*)vb_smem;
+  T* rbuf = eb + max(24 * (P.lv[lb].ex * P.lv[lb].ey * P.lv[lb].ez), 9 * 64 * ((P.ncoarse + 63) / 64));
+  auto V = [&](int l) -> VbLev<T> {
+    T* o = rbuf + 3 * P.lv[lb].n_nodes;
+    for (int m = lb; m < l; ++m) o += 6 * P.lv[m].n_nodes;
+    return vb_lev<T>(P.lv[l], o, o + 3 * P.lv[l].n_nodes);
+  };
+  {
+    const LevelDesc& L = P.lv[lb];
+    const auto* bg = gp(eb_ ? eb_ : fpool<T>(L) + (long long)C_B * L.stride);
+    const double sc = scale ? *scale : 1.0;
+    const VbLev<T> Vb = V(lb);
+    for (int q = threadIdx.x; q < 3 * Vb.nn; q += (int)blockDim.x) {
+      const int n = q / 3;
+      const bool fixed = n % Vb.NX == 0;
+      const T b0 = bg[3 * n] * sc, b1 = bg[3 * n + 1] * sc, b2 = bg[3 * n + 2] * sc;
+      Vb.b[q] = fixed ? T(0) : bg[q] * sc;
+      T x = T(0);
+      if (lb < Lc && !fixed) {
+        const T TG_GLOBAL* D = gp(fD<T>(L)) + 3LL * q;   // row q % 3 of the node's block
+        x = ch.om[lb][0] * mad_(D[2], b2, mad_(D[1], b1, D[0] * b0));
+      }
+      Vb.x[q] = x;
+    }
+    for (int l = lb + 1; l <= Lc; ++l) {
+      const VbLev<T> Vl = V(l);
+      for (int q = threadIdx.x; q < 3 * Vl.nn; q += (int)blockDim.x) Vl.x[q] = T(0);
+    }
+  }
+  __syncthreads();
+  for (int l = lb; l < Lc; ++l) {
+    const VbLev<T> Vl = V(l);
+    // x_0 = 0 before the first step, which is done
+    for (int q = threadIdx.x; q < 3 * Vl.nn; q += (int)blockDim.x) rbuf[q] = T(0);
+    __syncthreads();
+    for (int k = 1; k < nu_pre; ++k) vb_sweep<T, false, L1, true>(P, l, Vl, eb, rbuf, ch.om[l][k], ch.be[l][k]);
+    vb_sweep<T, true, L1>(P, l, Vl, eb, rbuf, T(0));
+    vb_restrict<T>(Vl, rbuf, P.lv[l + 1], V(l + 1), ch.om[l + 1][0], l + 1 < Lc);
+  }
+  vb_coarse<T>(P, V(Lc), eb);
+  for (int l = Lc - 1; l >= lb; --l) {
+    const VbLev<T> Vl = V(l);
+    vb_prolong<T>(Vl, V(l + 1));
+    for (int k = 0; k < nu_post; ++k) vb_sweep<T, false, L1, true>(P, l, Vl, eb, rbuf, ch.om[l][k], ch.be[l][k]);
+  }
+  const LevelDesc& L = P.lv[lb];
+  const VbLev<T> Vb = V(lb);
+  auto* yg = gp(ey_ ? ey_ : fpool<T>(L) + (long long)C_XA * L.stride);
+  for (int q = threadIdx.x; q < 3 * Vb.nn; q += (int)blockDim.x) yg[q] = Vb.x[q];
+}
+
 // Dynamic LDS the bottom kernel may take on the current device (the
 // per-workgroup limit less a margin), with both kernels' limits raised to it
 // once per device.
@@ -1528,8 +1718,9 @@ size_t vbottom_lds_limit() {
       v = 0;
     }
     size_t l = v > 1024 ? (size_t)v - 1024 : 0;
-    const void* kf[4] = {(const void*)k_vbottom<float, false>, (const void*)k_vbottom<float, true>,
-                         (const void*)k_vbottom<double, false>, (const void*)k_vbottom<double, true>};
+    const void* kf[6] = {(const void*)k_vbottom<float, false>, (const void*)k_vbottom<float, true>,
+                         (const void*)k_vbottom<double, false>, (const void*)k_vbottom<double, true>,
+                         (const void*)k_vbottom_cheb<false>, (const void*)k_vbottom_cheb<true>};
     bool ok = true;
     for (const void* k : kf)
       ok = ok && l && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l) == hipSuccess;
@@ -1543,6 +1734,16 @@ size_t vbottom_lds_limit() {
   return lim[dev];
 }
 
+int level_vbottom_cheb64(const Batch* b, const double (*om)[16], const double (*be)[16], const double* bb,
+                         const double* scale, double* y, int nu_pre, int nu_post, hipStream_t s) {
+  VbCheb ch;
+  std::memcpy(ch.om, om, sizeof(ch.om));
+  std::memcpy(ch.be, be, sizeof(ch.be));
+  (b->vb_l1[1] ? k_vbottom_cheb<true> : k_vbottom_cheb<false>)<<<b->vb[1].n, VbThreads<double, true>::N, b->vb_lds[1], s>>>(
+      b->desc_d, b->vb[1].ptr, ch, bb, scale, y, nu_pre, nu_post);
+  TG_HIP(hipGetLastError());
+  return TG_OK;
+}
 template <class T>
 int launch_vbottom(const Batch* b, const DevList& dl, size_t lds_bytes, int sfin, double omega, int nu_pre,
                    int nu_post, bool l1, hipStream_t s) {

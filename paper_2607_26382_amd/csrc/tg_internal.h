@@ -308,6 +308,43 @@ int level_restrict64(Batch* b, int l, const double* x, const double* bb, int slo
 int level_prolong64(Batch* b, int l, const double* ec, double* xf, hipStream_t s);
 int level_coarse64(Batch* b, int l, const double* bb, double* y, hipStream_t s);
 
+int level_apply_jacobi64(const Batch* b, const double* bb, const double* scale, double* z, double* y, hipStream_t s);
+int level_cheb_first64(const Batch* b, int l, const double* bb, const double* scale, double om0, double om1,
+                       double be1, double* y, double* bcopy, hipStream_t s);
+int level_cheb_step64(const Batch* b, int l, const double* x, const double* xp, const double* bb, double om, double be,
+                      double* y, hipStream_t s);
+int level_cheb_prolong64(const Batch* b, int l, const double* x, const double* e, const double* bb, double om,
+                         double* y, double* xo, hipStream_t s);
+
+// the Chebyshev V-cycle of levels vb_lb64.. in one launch (vb_lb64 must exist);
+// om, be: coefficients per level and step
+int level_vbottom_cheb64(const Batch* b, const double (*om)[16], const double (*be)[16], const double* bb,
+                         const double* scale, double* y, int nu_pre, int nu_post, hipStream_t s);
+
+// One Krylov process on caller memory with the batched delayed-CGS2 kernels:
+// slots 0..q of the pool hold V, slot q + 1 w, `stride` doubles apart (a
+// multiple of TG_VCHUNK, zero beyond 3 n_nodes).
+struct KrylovOne {
+  int q = 0, chunks = 0;
+  long long n = 0, stride = 0;
+  SmallLayout sl;
+  double* pool = nullptr;
+  double* small = nullptr;
+  double* part = nullptr;       // (2 q + 3) x chunks
+  double* status = nullptr;
+  int2* list = nullptr;         // chunks
+  ProbDesc* desc = nullptr;
+  double* V(int j) const { return pool + (long long)j * stride; }
+  double* W() const { return V(q + 1); }
+  double* Z(int j) const { return V(q + 2 + j); }
+  const double* scale() const { return small + sl.scal + SC_INV; }   // 1 / rho of the last vector
+};
+int krylov_bind(const KrylovOne& K, hipStream_t s);
+// V_0 = src (may be V_0), its squared norm also to *rr
+int krylov_start(const KrylovOne& K, const double* src, double* rr, hipStream_t s);
+int krylov_step(const KrylovOne& K, int j, hipStream_t s);       // column j from w = A z_j
+int krylov_finish(const KrylovOne& K, double* out, hipStream_t s);   // out = Z y
+
 // policy pieces shared by the fixed-cycle and the adaptive-stack policies
 // (tg_solver.hip, tg_mlp.hip): probe features from a history, Eq. trigger,
 // the network's first rung, the six density statistics

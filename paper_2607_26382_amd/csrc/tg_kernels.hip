@@ -2012,4 +2012,142 @@ int k_init_small(Batch* b, hipStream_t s) {
   return check_launch("init_small");
 }
 
+
+// ---------------------------------------------------------------------------
+// One Krylov process on caller memory (KrylovOne).
+// Bound by launches: a step is four of them, 25 us at 215 k unknowns, in place of
+// eleven (two dot products of three launches each, the updates, the rotations).
+static SmallOffs offs(const SmallLayout& s) {
+  return {s.mmax, s.H, s.g, s.cs, s.sn, s.y, s.h, s.tmp, s.scal, s.hist};
+}
+// the descriptor and the work list, and the slots' tails cleared
+__global__ __launch_bounds__(256) void k_kry_bind_(ProbDesc d, ProbDesc* desc, int2* list, int chunks, int slots) {
+  const LevelDesc& L = d.lv[0];
+  const long long n = 3LL * L.n_nodes;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) *desc = d;
+    for (int c = threadIdx.x; c < chunks; c += 256) list[c] = make_int2(0, c);
+  }
+  for (int v = blockIdx.x; v < slots; v += gridDim.x)
+    for (long long q = n + threadIdx.x; q < L.stride; q += 256) L.vec64[v * L.stride + q] = 0.0;
+}
+int krylov_bind(const KrylovOne& K, hipStream_t s) {
+  ProbDesc d = {};
+  d.nlev = 1;
+  d.small = K.small;
+  d.part = K.part;
+  d.lv[0].n_nodes = (int)(K.n / 3);
+  d.lv[0].n_chunks = K.chunks;
+  d.lv[0].stride = K.stride;
+  d.lv[0].vec64 = K.pool;
+  k_kry_bind_<<<std::min(64, K.q + 2), 256, 0, s>>>(d, K.desc, K.list, K.chunks, K.q + 2);
+  return check_launch("krylov bind");
+}
+// V_0 = src and the chunk sums of src . src
+__global__ __launch_bounds__(256) void k_kry_start_(const ProbDesc* __restrict__ probs, const double* src) {
+  __shared__ double sh[4];
+  const ProbDesc& P = *probs;
+  const LevelDesc& L = P.lv[0];
+  long long lo, hi;
+  chunk_range(L, blockIdx.x, lo, hi);
+  double* v = L.vec64;
+  double a = 0.0;
+#pragma unroll
+  for (int q = 0; q < TG_VCHUNK / 256; ++q) {
+    const long long i = lo + threadIdx.x + 256LL * q;
+    if (i < hi) {
+      const double x = src[i];
+      if (v != src) v[i] = x;
+      a += x * x;
+    }
+  }
+  a = block_sum256(a, sh);
+  if (threadIdx.x == 0) P.part[blockIdx.x] = a;
+}
+// beta = ||V_0||, then the cycle start (k_cycle_start_) with no tolerance
+__global__ __launch_bounds__(256) void k_kry_begin_(const ProbDesc* __restrict__ probs, SmallOffs o, double* rr,
+                                                    double* status) {
+  __shared__ double sh[4];
+  const ProbDesc& P = *probs;
+  const int nc = P.lv[0].n_chunks;
+  double a = 0.0;
+  for (int c = threadIdx.x; c < nc; c += 256) a += P.part[c];
+  a = block_sum256(a, sh);
+  double* S = P.small;
+  for (int q = threadIdx.x; q <= o.mmax; q += 256)
+    if (q) S[o.g + q] = 0.0;
+  if (threadIdx.x != 0) return;
+  double* sc = S + o.scal;
+  const double beta = sqrt(a);
+  const double st = !isfinite(beta) ? TG_NONFINITE : beta == 0.0 ? TG_PROJ_CONVERGED : TG_RUNNING;
+  *rr = a;
+  S[o.g] = beta;
+  sc[SC_BNORM] = sc[SC_BETA] = sc[SC_RHO] = beta;
+  sc[SC_INV] = beta > 0.0 ? 1.0 / beta : 0.0;
+  sc[SC_ITERS] = sc[SC_JDONE] = 0.0;
+  sc[SC_STATUS] = st;
+  *status = st;
+}
+int krylov_start(const KrylovOne& K, const double* src, double* rr, hipStream_t s) {
+  k_kry_start_<<<K.chunks, 256, 0, s>>>(K.desc, src);
+  k_kry_begin_<<<1, 256, 0, s>>>(K.desc, offs(K.sl), rr, K.status);
+  return check_launch("krylov start");
+}
+int krylov_step(const KrylovOne& K, int j, hipStream_t s) {
+  const SmallOffs o = offs(K.sl);
+  // (cap beyond the last column: its reorthogonalization follows in krylov_finish)
+  k_dots2_<false><<<K.chunks, 256, 0, s>>>(K.desc, K.list, 0, j, j, K.q + 1);
+  k_fin_a_<<<1, 256, 0, s>>>(K.desc, K.list, o, j, K.status);
+  k_update2_<false><<<K.chunks, 256, 0, s>>>(K.desc, K.list, 0, j, j, K.q + 1, j + 1, o.tmp);
+  k_fin_b_<<<1, 256, 0, s>>>(K.desc, K.list, o, j, K.q + 1, 0.0, 1e-14, K.status);
+  return check_launch("krylov step");
+}
+// y = R^-1 g over the columns done, by columns on one wave: lane i holds
+// entries i and i + 64 of the right-hand side
+__global__ __launch_bounds__(64) void k_kry_lsq_(const ProbDesc* __restrict__ probs, SmallOffs o) {
+  double* S = probs->small;
+  const int jd = (int)S[o.scal + SC_JDONE], ldh = o.mmax + 1, lane = threadIdx.x;
+  double v0 = lane < jd ? S[o.g + lane] : 0.0, v1 = lane + 64 < jd ? S[o.g + lane + 64] : 0.0;
+  const auto* H = gp((const double*)S + o.H);
+  auto col = [&](int c, double& r0, double& r1) {
+    r0 = c >= 0 && lane <= c ? H[(long long)ldh * c + lane] : 1.0;
+    r1 = c >= 0 && lane + 64 <= c ? H[(long long)ldh * c + lane + 64] : 1.0;
+  };
+  double r0, r1, n0, n1;
+  col(jd - 1, r0, r1);
+  for (int c = jd - 1; c >= 0; --c) {
+    col(c - 1, n0, n1);   // the next column is read ahead
+    const double y = __shfl((c < 64 ? v0 : v1) / (c < 64 ? r0 : r1), c & 63, 64);
+    if (lane < c) v0 -= r0 * y;
+    if (lane + 64 < c) v1 -= r1 * y;
+    if (lane == 0) S[o.y + c] = y;
+    r0 = n0;
+    r1 = n1;
+  }
+}
+// out = sum_{j < done} y_j Z_j
+__global__ __launch_bounds__(256) void k_kry_combine_(const double* __restrict__ Z, long long stride,
+                                                      const double* __restrict__ S, SmallOffs o, long long n,
+                                                      double* __restrict__ out) {
+  __shared__ double sy[TG_MAX_RESTART];
+  const int jd = (int)S[o.scal + SC_JDONE];
+  if ((int)threadIdx.x < jd) sy[threadIdx.x] = S[o.y + threadIdx.x];
+  __syncthreads();
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  double a = 0.0;
+#pragma unroll 4
+  for (int j = 0; j < jd; ++j) a += sy[j] * Z[j * stride + i];
+  out[i] = a;
+}
+int krylov_finish(const KrylovOne& K, double* out, hipStream_t s) {
+  const SmallOffs o = offs(K.sl);
+  // the last column's second pass (w is not needed: V_q itself)
+  k_dots2_<false><<<K.chunks, 256, 0, s>>>(K.desc, K.list, 0, K.q, K.q, K.q);
+  k_fin_a_<<<1, 256, 0, s>>>(K.desc, K.list, o, K.q, K.status);
+  k_kry_lsq_<<<1, 64, 0, s>>>(K.desc, o);
+  k_kry_combine_<<<(unsigned)((K.n + 255) / 256), 256, 0, s>>>(K.Z(0), K.stride, K.small, o, K.n, out);
+  return check_launch("krylov finish");
+}
+
 }  // namespace tg
