@@ -1303,6 +1303,14 @@ struct VbThreads {
   static constexpr int G = 8;
 };
 
+// Helper workgroups per problem (k_vbottom) and the CUs that they may fill, one
+// workgroup each.  Between two cycles of a solve the Gram-Schmidt sweeps push the
+// bottom's matrices (0.6 MB for a 16x8x8 level) out of the L2 cache, and one CU
+// gets them back slowly.  us per iteration with 0 / 2 / 4 / 8 helpers: 64x32x32
+// split 182.6 / 180.6 / 180.1 / 180.4, FP64 211.3 / 209.3 / 208.5 / 208.1; with the
+// matrices in the cache (cycles alone, 16x8x8) no difference.
+constexpr int VB_HELPERS = 4, VB_CUS = 256;
+
 // LDS words (of type T) the bottom needs from level lb of grid g down
 static size_t vb_words(const tg_grid* g, int lb) {
   const auto& H = g->lv[lb];
@@ -1408,7 +1416,9 @@ __device__ __forceinline__ void vb_elements(const ProbDesc& P, int l, const Leve
 }
 
 // (K x)_n from the element buffer: the elements around node (i, j, k) in the
-// order dk, dj, di
+// order dk, dj, di.  An element outside the grid is read at a clamped index and
+// counts +0 (the sum is never -0, so that is the same as leaving it out): eight
+// branches were eight waits for LDS in a row.
 template <class T>
 __device__ __forceinline__ void vb_gather(const VbLev<T>& V, const T* eb, int i, int j, int k, T* kx) {
   kx[0] = kx[1] = kx[2] = T(0);
@@ -1419,11 +1429,14 @@ __device__ __forceinline__ void vb_gather(const VbLev<T>& V, const T* eb, int i,
 #pragma unroll
       for (int di = 0; di < 2; ++di) {
         const int ei = i - 1 + di, ej = j - 1 + dj, ek = k - 1 + dk;
-        if (ei < 0 || ei >= V.ex || ej < 0 || ej >= V.ey || ek < 0 || ek >= V.ez) continue;
-        const int e = ei + V.ex * (ej + V.ey * ek);
+        const bool in = ei >= 0 && ei < V.ex && ej >= 0 && ej < V.ey && ek >= 0 && ek < V.ez;
+        const int e = in ? ei + V.ex * (ej + V.ey * ek) : 0;
         const int a = (1 - di) + 2 * (1 - dj) + 4 * (1 - dk);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) kx[c] += eb[(3 * a + c) * V.ne + e];
+        for (int c = 0; c < 3; ++c) {
+          const T v = eb[(3 * a + c) * V.ne + e];
+          kx[c] += in ? v : T(0);
+        }
       }
 }
 
@@ -1432,17 +1445,31 @@ __device__ __forceinline__ void vb_gather(const VbLev<T>& V, const T* eb, int i,
 // is updated in place), or r = b - K x into rbuf (RESID = true); clamped
 // nodes 0.  CH: a Chebyshev step, x <- x + w D^-1 (b - K x) + beta (x - xp)
 // with the previous iterate xp in rbuf, which takes x (beta = 0: xp unused).
+// The diagonal blocks of a thread's first two nodes are on their way while the
+// element pass ends.
 template <class T, bool RESID, bool L1, bool CH = false>
 __device__ void vb_sweep(const ProbDesc& P, int l, const VbLev<T>& V, T* eb, T* rbuf, T omega, T beta = T(0)) {
   const LevelDesc& L = P.lv[l];
   vb_elements<T, L1>(P, l, L, V, eb);
+  const int tid = threadIdx.x, nt = (int)blockDim.x;
+  const T TG_GLOBAL* Dg = gp(fD<T>(L));
+  T D[2][9];
+  auto load = [&](int n, T* d) {
+    const T TG_GLOBAL* p = Dg + 9LL * min(n, V.nn - 1);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) d[q] = p[q];
+  };
+  if constexpr (!RESID) {
+    load(tid, D[0]);
+    if (nt < V.nn) load(tid + nt, D[1]);
+  }
   __syncthreads();
-  for (int n = threadIdx.x; n < V.nn; n += (int)blockDim.x) {
+  auto node = [&](int n, const T* d) {
     const int i = n % V.NX, t = n / V.NX, j = t % V.NY, k = t / V.NY;
     T* dst = RESID ? rbuf : V.x;
     if (i == 0) {
       if (RESID) dst[3 * n] = dst[3 * n + 1] = dst[3 * n + 2] = T(0);
-      continue;
+      return;
     }
     T kx[3];
     vb_gather<T>(V, eb, i, j, k, kx);
@@ -1452,11 +1479,10 @@ __device__ void vb_sweep(const ProbDesc& P, int l, const VbLev<T>& V, T* eb, T* 
       dst[3 * n + 1] = r1;
       dst[3 * n + 2] = r2;
     } else {
-      const T TG_GLOBAL* D = gp(fD<T>(L)) + 9LL * n;
       T xn[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c)
-        xn[c] = mad_(omega, mad_(D[3 * c + 2], r2, mad_(D[3 * c + 1], r1, D[3 * c] * r0)), V.x[3 * n + c]);
+        xn[c] = mad_(omega, mad_(d[3 * c + 2], r2, mad_(d[3 * c + 1], r1, d[3 * c] * r0)), V.x[3 * n + c]);
       if constexpr (CH) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -1468,6 +1494,12 @@ __device__ void vb_sweep(const ProbDesc& P, int l, const VbLev<T>& V, T* eb, T* 
 #pragma unroll
       for (int c = 0; c < 3; ++c) dst[3 * n + c] = xn[c];
     }
+  };
+  if (tid < V.nn) node(tid, D[0]);
+  if (tid + nt < V.nn) node(tid + nt, D[1]);
+  for (int n = tid + 2 * nt; n < V.nn; n += nt) {
+    if constexpr (!RESID) load(n, D[0]);
+    node(n, D[0]);
   }
   __syncthreads();
 }
@@ -1480,28 +1512,34 @@ __device__ void vb_restrict(const VbLev<T>& F, const T* r, const LevelDesc& Lc, 
   for (int n = threadIdx.x; n < C.nn; n += (int)blockDim.x) {
     const int I = n % C.NX, t = n / C.NX, J = t % C.NY, K = t / C.NY;
     T s[3] = {T(0), T(0), T(0)};
-    if (I > 0) {
-      for (int dk = -1; dk <= 1; ++dk) {
-        const int k = 2 * K + dk;
-        if (k < 0 || k >= F.NZ) continue;
-        for (int dj = -1; dj <= 1; ++dj) {
-          const int j = 2 * J + dj;
-          if (j < 0 || j >= F.NY) continue;
-          for (int di = -1; di <= 1; ++di) {
-            const int i = 2 * I + di;
-            if (i < 0 || i >= F.NX) continue;
-            const T w = T(1) / T(1 << ((di != 0) + (dj != 0) + (dk != 0)));
-            const int f = i + F.NX * (j + F.NY * k);
+    T D[9];
+    if (first_sweep) {
+      const T TG_GLOBAL* Dg = gp(fD<T>(Lc)) + 9LL * n;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) s[c] = mad_(w, r[3 * f + c], s[c]);
+      for (int q = 0; q < 9; ++q) D[q] = Dg[q];
+    }
+    // taps outside the grid are read at the node itself and count zero
+    if (I > 0) {
+#pragma unroll
+      for (int dk = -1; dk <= 1; ++dk)
+#pragma unroll
+        for (int dj = -1; dj <= 1; ++dj)
+#pragma unroll
+          for (int di = -1; di <= 1; ++di) {
+            const int i = 2 * I + di, j = 2 * J + dj, k = 2 * K + dk;
+            const bool in = k >= 0 && k < F.NZ && j >= 0 && j < F.NY && i < F.NX;
+            const T w = T(1) / T(1 << ((di != 0) + (dj != 0) + (dk != 0)));
+            const int f = in ? i + F.NX * (j + F.NY * k) : 2 * I + F.NX * (2 * J + F.NY * 2 * K);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const T v = r[3 * f + c];
+              s[c] = mad_(w, in ? v : T(0), s[c]);
+            }
           }
-        }
-      }
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) C.b[3 * n + c] = s[c];
     if (first_sweep) {
-      const T TG_GLOBAL* D = gp(fD<T>(Lc)) + 9LL * n;
 #pragma unroll
       for (int c = 0; c < 3; ++c)
         C.x[3 * n + c] = omega * mad_(D[3 * c + 2], s[2], mad_(D[3 * c + 1], s[1], D[3 * c] * s[0]));
@@ -1521,14 +1559,13 @@ __device__ void vb_prolong(const VbLev<T>& F, const VbLev<T>& C) {
     T s0 = T(0), s1 = T(0), s2 = T(0);
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      if ((c & 1) && !(i & 1)) continue;
-      if ((c & 2) && !(j & 1)) continue;
-      if ((c & 4) && !(k & 1)) continue;
+      const bool in = !((c & 1) && !(i & 1)) && !((c & 2) && !(j & 1)) && !((c & 4) && !(k & 1));
       const int I = (c & 1) ? i1 : i0, J = (c & 2) ? j1 : j0, K = (c & 4) ? k1 : k0;
-      const int m = I + C.NX * (J + C.NY * K);
-      s0 = mad_(w, C.x[3 * m], s0);
-      s1 = mad_(w, C.x[3 * m + 1], s1);
-      s2 = mad_(w, C.x[3 * m + 2], s2);
+      const int m = I + C.NX * (J + C.NY * K);   // (in the grid also where it does not count)
+      const T x0 = C.x[3 * m], x1 = C.x[3 * m + 1], x2 = C.x[3 * m + 2];
+      s0 = mad_(w, in ? x0 : T(0), s0);
+      s1 = mad_(w, in ? x1 : T(0), s1);
+      s2 = mad_(w, in ? x2 : T(0), s2);
     }
     F.x[3 * n] += s0;
     F.x[3 * n + 1] += s1;
@@ -1552,14 +1589,29 @@ __device__ void vb_coarse(const ProbDesc& P, const VbLev<T>& C, T* buf) {
   auto node_of = [&](int q) { const int f = q / 3, t = f / NXm; return 3 * (f - t * NXm + 1 + C.NX * t) + q - 3 * f; };
   T* sb = buf;                  // b by free index
   T* sp = buf + 64 * ng;        // partial sums: part, row
+  // a wave's first sixteen entries are read ahead of b
+  const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  T pre[16];
+  {
+    const T TG_GLOBAL* col = Ci + min((w0 >> 3) * 64 + lane, n - 1);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) pre[u] = col[(long long)min((w0 & 7) + 8 * u, n - 1) * n];
+  }
   for (int q = threadIdx.x; q < n; q += (int)blockDim.x) sb[q] = C.b[node_of(q)];
   __syncthreads();
-  for (int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < 8 * ng; w += (int)blockDim.x >> 6) {
+  for (int w = w0; w < 8 * ng; w += (int)blockDim.x >> 6) {
     const int part = w & 7, q = (w >> 3) * 64 + lane;
     T s = T(0);
     const T TG_GLOBAL* col = Ci + min(q, n - 1);
+    int c = part;
+    if (w == w0) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (part + 8 * u < n) s = mad_(pre[u], sb[part + 8 * u], s);
+      c += 128;
+    }
 #pragma unroll 16
-    for (int c = part; c < n; c += 8) s = mad_(col[(long long)c * n], sb[c], s);
+    for (; c < n; c += 8) s = mad_(col[(long long)c * n], sb[c], s);
     sp[part * 64 * ng + q] = s;
   }
   __syncthreads();
@@ -1571,17 +1623,57 @@ __device__ void vb_coarse(const ProbDesc& P, const VbLev<T>& C, T* buf) {
   __syncthreads();
 }
 
+// Reads one word of every 128 bytes of [p, p + bytes) that falls to this helper
+// (part of parts), four under way at a time; the words are dropped.
+__device__ __forceinline__ void vb_touch(const void* p, long long bytes, int part, int parts) {
+  const char TG_GLOBAL* c = gp((const char*)p);
+  const long long lines = bytes >> 7, step = (long long)parts * blockDim.x;
+  for (long long i = part * (long long)blockDim.x + threadIdx.x; i < lines; i += 4 * step) {
+    unsigned v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *(const unsigned TG_GLOBAL*)(c + (min(i + u * step, lines - 1) << 7));
+    asm volatile("" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+  }
+}
+// A helper workgroup: brings what the problem's bottom reads of level lb and
+// below into the L2 cache of the XCD that it runs on.
+template <class T>
+__device__ void vb_warm(const ProbDesc& P, int lb, int part, int parts) {
+  const int Lc = P.nlev - 1;
+  for (int l = lb; l < Lc; ++l) {
+    const LevelDesc& L = P.lv[l];
+    const int ne = L.ex * L.ey * L.ez;
+    if (l > TG_MF_LEVELS)
+      vb_touch(fKm<T>(L), (long long)((ne + 63) / 64) * 64 * TG_GM_STRIDE * sizeof(T), part, parts);
+    vb_touch(fD<T>(L), 9LL * L.n_nodes * sizeof(T), part, parts);
+  }
+  vb_touch(vb_cinv<T>(P), (long long)P.ncoarse * P.ncoarse * sizeof(T), part, parts);
+}
+
+// Bounded by what one CU issues and loads: a 16x8x8 pass is 1024 elements of 570
+// instructions and 0.6 MB, 6 us, and its node sums 2 us; the rest is chains of LDS
+// and cache latencies, hence the loads ahead of the barriers and the sums without
+// branches.  Cycle of 64x32x32 split / FP64: 127.3 -> 122.6 / 146.7 -> 142.5 us.
+// Workgroups are dealt to the eight XCDs in turn, so those of one problem and its
+// helpers, a multiple of eight apart, share an L2 cache; a wrong guess would cost
+// the helpers' use, nothing else.
 // L1: some problem of the launch starts at level 1 (the moment-form
 // operator is compiled in only then: it costs registers)
 template <class T, bool L1>
 __global__ __launch_bounds__((VbThreads<T, L1>::N)) void k_vbottom(const ProbDesc* __restrict__ probs,
                                                         const int2* __restrict__ work, int sfin, T omega,
-                                                        int nu_pre, int nu_post) {
+                                                        int nu_pre, int nu_post, int n, int n8) {
   extern __shared__ __align__(16) unsigned char vb_smem[];
-  const int2 wi = work[blockIdx.x];
-  const ProbDesc& P = probs[wi.x];
+  // problem p: workgroup p, its helpers p + n8, p + 2 n8, ..
+  const int p = (int)blockIdx.x % n8, part = (int)blockIdx.x / n8;
+  if (p >= n) return;
+  const ProbDesc& P = probs[work[p].x];
   TG_GATE(P);
   const int lb = sizeof(T) == 8 ? P.vb_lb64 : P.vb_lb32;
+  if (part) {
+    vb_warm<T>(P, lb, part - 1, (int)gridDim.x / n8 - 1);
+    return;
+  }
   const int Lc = P.nlev - 1;
   T* eb = (T*)vb_smem;
   T* rbuf = eb + max(24 * (P.lv[lb].ex * P.lv[lb].ey * P.lv[lb].ez), 9 * 64 * ((P.ncoarse + 63) / 64));
@@ -1599,13 +1691,26 @@ __global__ __launch_bounds__((VbThreads<T, L1>::N)) void k_vbottom(const ProbDes
     const T TG_GLOBAL* xg = gp(fpool<T>(L) + (long long)C_XA * L.stride);
     const bool first = lb < Lc;
     const VbLev<T> Vb = V(lb);
-    for (int q = threadIdx.x; q < 3 * Vb.nn; q += (int)blockDim.x) {
-      Vb.b[q] = bg[q];
-      Vb.x[q] = first ? xg[q] : T(0);
-    }
     for (int l = lb + 1; l <= Lc; ++l) {
       const VbLev<T> Vl = V(l);
       for (int q = threadIdx.x; q < 3 * Vl.nn; q += (int)blockDim.x) Vl.x[q] = T(0);
+    }
+    // five loads of each vector under way at a time
+    for (int q0 = threadIdx.x; q0 < 3 * Vb.nn; q0 += 5 * (int)blockDim.x) {
+      T bv[5], xv[5];
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        const int q = min(q0 + u * (int)blockDim.x, 3 * Vb.nn - 1);
+        bv[u] = bg[q];
+        xv[u] = first ? xg[q] : T(0);
+      }
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        const int q = q0 + u * (int)blockDim.x;
+        if (q >= 3 * Vb.nn) break;
+        Vb.b[q] = bv[u];
+        Vb.x[q] = xv[u];
+      }
     }
   }
   __syncthreads();
@@ -1748,10 +1853,10 @@ template <class T>
 int launch_vbottom(const Batch* b, const DevList& dl, size_t lds_bytes, int sfin, double omega, int nu_pre,
                    int nu_post, bool l1, hipStream_t s) {
   if (!dl.n) return TG_OK;
-  if (l1)
-    k_vbottom<T, true><<<dl.n, VbThreads<T, true>::N, lds_bytes, s>>>(b->desc_d, dl.ptr, sfin, T(omega), nu_pre, nu_post);
-  else
-    k_vbottom<T, false><<<dl.n, VbThreads<T, false>::N, lds_bytes, s>>>(b->desc_d, dl.ptr, sfin, T(omega), nu_pre, nu_post);
+  const int n8 = (dl.n + 7) / 8 * 8;
+  const int parts = std::max(0, std::min(VB_HELPERS, VB_CUS / n8 - 1));
+  (l1 ? k_vbottom<T, true> : k_vbottom<T, false>)<<<n8 * parts + (parts ? n8 : dl.n), VbThreads<T, true>::N, lds_bytes, s>>>(
+      b->desc_d, dl.ptr, sfin, T(omega), nu_pre, nu_post, dl.n, n8);
   return TG_OK;
 }
 template int launch_vbottom<float>(const Batch*, const DevList&, size_t, int, double, int, int, bool, hipStream_t);
