@@ -164,7 +164,6 @@ static void grid_layout(tg_grid* g, Bump& bp, int mmax) {
   D.Ke64 = bp.take<double>(576);
   D.Ke32 = bp.take<float>(576);
   D.G64 = bp.take<double>(8 * 576);
-  D.Pc64 = bp.take<double>(8 * 576);
   D.G1v64 = bp.take<double>(TG_G1_NVAL);
   D.G1v32 = bp.take<float>(TG_G1_NVAL);
   D.E64 = bp.take<double>(g->lv[0].n_elem);
@@ -361,7 +360,8 @@ int batch_set_active(Batch* b, const std::vector<int>& active, hipStream_t s, bo
       for (int p : active) {
         tg_grid* g = b->grids[p];
         if (l >= g->nlev) continue;
-        const long long cnt = (l == 0) ? (g->lv[0].n_elem + 255) / 256 : g->lv[l].n_elem;
+        const int ch = l == 0 ? 256 : setup_chunk(g->lv[l].n_elem);
+        const long long cnt = (g->lv[l].n_elem + ch - 1) / ch;
         for (long long t = 0; t < cnt; ++t) H.push_back(make_int2(p, (int)t));
       }
     }
@@ -550,7 +550,6 @@ int grid_bind(tg_grid* g, void* ws, size_t bytes, int mmax) {
   TG_HIP(hipMemcpy((void*)g->desc.Ke64, g->Ke, sizeof(g->Ke), hipMemcpyHostToDevice));
   TG_HIP(hipMemcpy((void*)g->desc.Ke32, ke32, sizeof(ke32), hipMemcpyHostToDevice));
   TG_HIP(hipMemcpy((void*)g->desc.G64, g->G, sizeof(g->G), hipMemcpyHostToDevice));
-  TG_HIP(hipMemcpy((void*)g->desc.Pc64, g->Pc, sizeof(g->Pc), hipMemcpyHostToDevice));
   float g1v32[TG_G1_NVAL];
   for (int q = 0; q < TG_G1_NVAL; ++q) g1v32[q] = (float)g->g1v[q];
   TG_HIP(hipMemcpy((void*)g->desc.G1v64, g->g1v, sizeof(g->g1v), hipMemcpyHostToDevice));

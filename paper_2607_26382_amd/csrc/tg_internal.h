@@ -19,6 +19,12 @@
 
 #define TG_MAXLEV 8
 #define TG_NODE_TILE 256     // nodes per workgroup for node-centred kernels
+// Elements of a Galerkin level per workgroup of the set-up kernels: one while a
+// level does not fill the device, else eight.  Set-up with eight from 16384 / 6000 /
+// 3000 elements on: 128x64x64 362 / 393 / 394 us, 256x128x128 2234 / 2260 / 2261,
+// 64x32x32 158 / 155 / 148.
+#define TG_SETUP_CHUNK 8
+__host__ __device__ inline int setup_chunk(long long n_elem) { return n_elem >= 16384 ? TG_SETUP_CHUNK : 1; }
 #define TG_VCHUNK 2048       // DOFs per workgroup for vector kernels
 #define TG_VBLOCK 256        // threads per vector workgroup
 #define TG_PART_W 256        // max partial sums of one sweep (2 max_restart + 3)
@@ -104,7 +110,6 @@ struct ProbDesc {
   const double* Ke64;       // shared element stiffness (576)
   const float* Ke32;
   const double* G64;        // 8 x 576: child Galerkin matrices P_c^T Ke P_c
-  const double* Pc64;       // 8 x 576: child prolongations P_c (fine 24 x coarse 24)
   const double* G1v64;      // TG_G1_NVAL values of the level-1 moment matrices
   const float* G1v32;
   double* small;            // per-problem FGMRES scalars (SmallLayout)
