@@ -197,7 +197,7 @@ static void grid_layout(tg_grid* g, Bump& bp, int mmax) {
   const size_t nc = g->ncoarse;
   D.Cinv64 = bp.take<double>(nc * nc);
   D.Cinv32 = bp.take<float>(nc * nc);
-  D.Cwork = bp.take<double>(2 * nc * nc);
+  D.Cwork = bp.take<double>(std::max<size_t>(2 * nc * nc, 256 * (size_t)ci_tiles((int)nc)));
   g->sl.init(mmax, TG_HIST_CAP);
   D.small = bp.take<double>(g->sl.total);
   D.part = bp.take<double>((size_t)TG_PART_W * g->lv[0].n_chunks);

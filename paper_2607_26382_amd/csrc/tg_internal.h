@@ -81,6 +81,9 @@ int hip_fail(hipError_t e, const char* what);
 // ---------------------------------------------------------------------------
 // Per-level device view.  Vectors at a level live in two slot pools (FP64 and
 // FP32); slot s of a problem sits at pool + s * stride.
+// lower 16 x 16 tiles of a coarsest matrix of n free DOFs
+__host__ __device__ inline int ci_tiles(int n) { return (n + 15) / 16 * ((n + 15) / 16 + 1) / 2; }
+
 struct LevelDesc {
   int ex, ey, ez;           // elements
   int NX, NY, NZ;           // nodes per dimension (= elements + 1)

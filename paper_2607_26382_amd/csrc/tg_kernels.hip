@@ -333,43 +333,6 @@ __device__ __forceinline__ void nodeblock(const ProbDesc& P, int l, int n) {
   }
 }
 
-// The node blocks of every level and the mode-basis elements of the stored
-// ones, in one launch: all of them read the finished element matrices only.
-// Workgroups [end of the list before, end[u]) take list u (level u's nodes
-// for u < TG_MAXLEV, level u - TG_MAXLEV's elements from there).  At 48x24x24 14.9 us in place of
-// six launches, 72 us; at 256x128x128 883 us, 1277 before.
-struct SetupTail {
-  const int2* list[2 * TG_MAXLEV];
-  int end[2 * TG_MAXLEV];
-};
-__global__ __launch_bounds__(256) void k_setup_tail(const ProbDesc* __restrict__ probs, SetupTail w) {
-  __shared__ double sX[576];
-  int u = 0, b0 = 0;
-#pragma unroll
-  for (int q = 0; q < 2 * TG_MAXLEV - 1; ++q)
-    if ((int)blockIdx.x >= w.end[q]) {
-      u = q + 1;
-      b0 = w.end[q];
-    }
-  const int2* list = w.list[0];
-#pragma unroll
-  for (int q = 1; q < 2 * TG_MAXLEV; ++q)
-    if (u == q) list = w.list[q];
-  const int2 wi = list[blockIdx.x - b0];
-  const ProbDesc& P = probs[wi.x];
-  if (u < TG_MAXLEV) {
-    nodeblock(P, u, wi.y * TG_NODE_TILE + threadIdx.x);
-    return;
-  }
-  const LevelDesc& L = P.lv[u - TG_MAXLEV];
-  const long long ne = (long long)L.ex * L.ey * L.ez, e0 = (long long)wi.y * setup_chunk(ne);
-  const long long e1 = e0 + setup_chunk(ne) < ne ? e0 + setup_chunk(ne) : ne;
-  for (long long e = e0; e < e1; ++e) {
-    if (e > e0) __syncthreads();
-    mode_pack(L, e, sX);
-  }
-}
-
 // Node coordinates and component of a free DOF of the coarsest level, one byte
 // each (i, j, k, component); a level of at most TG_MAX_COARSE free DOFs has
 // fewer than 256 nodes in every dimension.
@@ -411,6 +374,67 @@ __device__ __forceinline__ double coarse_entry(const ProbDesc& P, const LevelDes
 #pragma unroll
   for (int a = 7; a >= 0; --a) s += in[a] ? E[a] * k[a] : 0.0;
   return pad ? unit : s;
+}
+
+// The node blocks of every level, the mode-basis elements of the stored ones and
+// the assembled coarsest matrices, in one launch: all of them read the finished
+// element matrices only.
+// Workgroups [end of the list before, end[u]) take list u (level u's nodes
+// for u < TG_MAXLEV, level u - TG_MAXLEV's elements from there), those behind them
+// a 16 x 16 tile of a problem's coarsest matrix each, which k_coarse_inverse reads
+// (assembled by that kernel's one workgroup, 322 us at n = 288 in place of 265).  At 48x24x24 14.9 us in place of
+// six launches, 72 us; at 256x128x128 883 us, 1277 before.
+struct SetupTail {
+  const int2* list[2 * TG_MAXLEV];
+  int end[2 * TG_MAXLEV];
+  const int2* prob;
+  int tiles;                // per problem, of the largest
+};
+// Tile t (row I, column J: t = I (I + 1) / 2 + J) to Cwork + 256 t, in the layout
+// of the matrix cores' results.
+__device__ __forceinline__ void coarse_tile(const ProbDesc& P, int t) {
+  const int n = P.ncoarse, T = (n + 15) >> 4;
+  if (t >= T * (T + 1) / 2) return;
+  int I = 0;
+  while ((I + 1) * (I + 2) / 2 <= t) ++I;
+  const int J = t - I * (I + 1) / 2, lane = threadIdx.x & 63;
+  const LevelDesc& L = P.lv[P.nlev - 1];
+  const int r = 16 * I + (lane >> 4) + 4 * (threadIdx.x >> 6), c = 16 * J + (lane & 15);
+  const int hi = max(r, c), lo = min(r, c);
+  P.Cwork[t * 256 + threadIdx.x] = coarse_entry(P, L, P.nlev == 1, n, hi, lo, coarse_dof(L, hi), coarse_dof(L, lo));
+}
+__global__ __launch_bounds__(256) void k_setup_tail(const ProbDesc* __restrict__ probs, SetupTail w) {
+  __shared__ double sX[576];
+  const int nb = w.end[2 * TG_MAXLEV - 1];
+  if ((int)blockIdx.x >= nb) {
+    const int q = (int)blockIdx.x - nb;
+    coarse_tile(probs[w.prob[q / w.tiles].x], q % w.tiles);
+    return;
+  }
+  int u = 0, b0 = 0;
+#pragma unroll
+  for (int q = 0; q < 2 * TG_MAXLEV - 1; ++q)
+    if ((int)blockIdx.x >= w.end[q]) {
+      u = q + 1;
+      b0 = w.end[q];
+    }
+  const int2* list = w.list[0];
+#pragma unroll
+  for (int q = 1; q < 2 * TG_MAXLEV; ++q)
+    if (u == q) list = w.list[q];
+  const int2 wi = list[blockIdx.x - b0];
+  const ProbDesc& P = probs[wi.x];
+  if (u < TG_MAXLEV) {
+    nodeblock(P, u, wi.y * TG_NODE_TILE + threadIdx.x);
+    return;
+  }
+  const LevelDesc& L = P.lv[u - TG_MAXLEV];
+  const long long ne = (long long)L.ex * L.ey * L.ez, e0 = (long long)wi.y * setup_chunk(ne);
+  const long long e1 = e0 + setup_chunk(ne) < ne ? e0 + setup_chunk(ne) : ne;
+  for (long long e = e0; e < e1; ++e) {
+    if (e > e0) __syncthreads();
+    mode_pack(L, e, sX);
+  }
 }
 
 // One 64-bit value of lane `lane` (a constant), in every lane of the wave.
@@ -465,32 +489,52 @@ __device__ __forceinline__ void ldl_block(double* a, double* m, int lane, double
 // accurate as a Cholesky elimination; its explicit inverse would not.)  No
 // pivoting: the pivots are diagonal entries of successive Schur complements,
 // positive for an SPD matrix (a non-positive one flags the problem).
-// What bounds it is the chain of n pivots: each 16 of them are done by one
-// wave in registers (row and column of the pivot by lane moves), beside the
-// other waves' matrix-core update of the previous block, so a block pivot
-// costs two barriers.  One element-by-element Gauss-Jordan pivot per barrier
-// took 170 us at n = 108, and the global-memory Cholesky that n > 141 used
-// took 22.9 ms at n = 288; this form takes 47 and 324 us.
-// LDS = true holds the tiles in LDS (n <= CI_LDS_N, where they fit beside the
-// panel); otherwise they live in the problem's work array, which one
-// workgroup's waves keep in cache.
+// What bounds it is the chain of n pivots at small n: each 16 of them are done by
+// one wave in registers (row and column of the pivot by lane moves, 3 to 5 us),
+// beside the other waves' matrix-core update of the previous block, so a block
+// pivot costs two barriers; from n = 200 or so that update (171 tiles at n = 288,
+// 4.6 us of one CU's FP64 matrix rate).  One element-by-element Gauss-Jordan
+// pivot per barrier took 170 us at n = 108, and the global-memory Cholesky that
+// n > 141 used took 22.9 ms at n = 288; this form takes 38 and 244 us (47 and 322
+// with the matrix assembled by the one workgroup and no tile skipped).
+// Where the tiles are: in LDS up to CI_LDS_N, where all fit beside the panel; up
+// to CI_REG_N most of those left of the diagonal in registers, 8 a wave, the rest
+// in LDS; beyond, in the problem's work array, which one workgroup's waves keep in
+// cache (n = 288 that way: 265 us).
 // Lane layouts of v_mfma_f64_16x16x4 (measured on gfx950): A[i][k] and
 // B[k][j] at lane i (j) + 16 k; D[i][j] at lane 16 (i % 4) + j, element i / 4.
 // A tile is stored in the D layout; slot s of lane group c is k = c + 4 s in
 // every product.
 #define CI_THREADS 1024
 #define CI_LDS_N 144    // 45 tiles (92 KB) and a 20 KB panel
+#define CI_REG_N 288    // 171 tiles: 120 in registers, 51 in LDS (105 KB) beside a 42 KB panel
+#define CI_SLOTS 8      // tiles that a wave holds in registers
+enum { CI_LDS = 0, CI_REG = 1, CI_MEM = 2 };
 #define CI_LD 18        // panel row stride (16 columns, padded)
 #define CI_M (16 * CI_LD + 16)   // M and 1 / p of a block pivot
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-__host__ __device__ inline size_t ci_lds_words(int n, bool tiles_in_lds) {
-  const int T = (n + 15) / 16;
-  // panel, two M blocks, tile order and DOF coordinates (32-bit each), tiles
-  return (size_t)16 * T * CI_LD + 2 * CI_M + (T * (T + 1) / 2 + 16 * T + 1) / 2 +
-         (tiles_in_lds ? (size_t)T * (T + 1) / 2 * 256 : 0);
+// tiles left of the diagonal that the register form holds in registers
+__host__ __device__ inline int ci_reg_tiles(int T) {
+  const int off = T * (T - 1) / 2, cap = CI_SLOTS * (CI_THREADS / 64 - 1);
+  return off < cap ? off : cap;
+}
+__host__ __device__ inline size_t ci_lds_words(int n, int form) {
+  const int T = (n + 15) / 16, NT = T * (T + 1) / 2;
+  // panel, two M blocks, tile order and panel flags (32-bit each), tiles
+  return (size_t)16 * T * CI_LD + 2 * CI_M + (NT + T + 1) / 2 +
+         256 * (size_t)(form == CI_LDS ? NT : form == CI_REG ? NT - ci_reg_tiles(T) : 0);
 }
 
-template <bool LDS>
+// f(0), .., f(N - 1) with constant arguments (register arrays need constant indices)
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void ci_each(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>());
+    ci_each<N, I + 1>(f);
+  }
+}
+
+template <int FORM>
 __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* __restrict__ probs,
                                                                const int2* __restrict__ work, int* bad, int nlo,
                                                                int nhi) {
@@ -499,33 +543,52 @@ __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* _
   const ProbDesc& P = probs[wi.x];
   const int n = P.ncoarse;
   if (n == 0 || n < nlo || n > nhi) return;   // no direct coarsest level, or the other form's size
-  const LevelDesc& L = P.lv[P.nlev - 1];
-  const bool fine = P.nlev == 1;
   const int T = (n + 15) >> 4, NT = T * (T + 1) / 2;
   double* G = smem;                       // panel: row r, column k at r CI_LD + k
   double* sM = G + 16 * T * CI_LD;        // M, same row stride, then 1 / p; of even and odd block pivots
   int* sT = (int*)(sM + 2 * CI_M);      // tile u in column order: I | J << 8
-  int* sN = sT + NT;                      // coarse_dof of every free DOF
-  double* A = LDS ? sM + 2 * CI_M + (NT + 16 * T + 1) / 2 : P.Cwork;
+  int* sZ = sT + NT;                      // whether tile row I of the panel is not all zero
+  double* A = FORM != CI_MEM ? sM + 2 * CI_M + (NT + T + 1) / 2 : P.Cwork;
   // (wave: uniform, so that tile indices and addresses stay scalar)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lj = lane & 15, lc = lane >> 4;
   constexpr int NW = CI_THREADS / 64;
+  // Register form: the tiles left of the diagonal in column order; wave 1 + v % 15
+  // has tile v, in slot v / 15 while v < NR, else in LDS behind the T diagonal
+  // tiles.  Wave 0 has none: it factors.
+  const int NO = NT - T, NR = ci_reg_tiles(T);
+  auto off_of = [&](int v) -> int {   // I | J << 8
+    int J = 0, u = v;
+    while (u >= T - 1 - J) u -= T - 1 - J++;
+    return (J + 1 + u) | J << 8;
+  };
+  auto place = [&](int I, int J) -> int {
+    if (FORM != CI_REG) return I * (I + 1) / 2 + J;
+    return I == J ? I : T + J * (T - 1) - J * (J - 1) / 2 + I - J - 1 - NR;
+  };
   for (int q = threadIdx.x; q < T * T; q += CI_THREADS) {
     const int J = q / T, I = q - J * T;
     if (I >= J) sT[J * T - J * (J - 1) / 2 + I - J] = I | J << 8;
   }
-  for (int q = threadIdx.x; q < 16 * T; q += CI_THREADS) sN[q] = coarse_dof(L, q);
+  if (threadIdx.x < T) sZ[threadIdx.x] = 0;
   __syncthreads();
   auto tile_of = [&](int u) -> int { return __builtin_amdgcn_readfirstlane(sT[u]); };
-  for (int u = wave; u < NT; u += NW) {
-    const int ij = tile_of(u), I = ij & 255, J = ij >> 8, t = I * (I + 1) / 2 + J;
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  // the assembled tiles (k_setup_tail) from the work array; the register form's
+  // waves fetch their own below
+  if constexpr (FORM != CI_MEM)
+    for (int u = wave; u < NT; u += NW) {
+      const int ij = tile_of(u), I = ij & 255, J = ij >> 8, t = place(I, J);
+      const bool reg = FORM == CI_REG && t < T && I != J;
+      const double* w = P.Cwork + 256 * (I * (I + 1) / 2 + J);
+      if (!reg)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int r = 16 * I + lc + 4 * v, c = 16 * J + lj, hi = max(r, c), lo = min(r, c);
-      A[t * 256 + 64 * v + lane] = coarse_entry(P, L, fine, n, hi, lo, sN[hi], sN[lo]);
+        for (int v = 0; v < 4; ++v) A[t * 256 + 64 * v + lane] = w[64 * v + lane];
     }
-  }
+  auto put = [&](int t, const f64x4& c) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) A[t * 256 + 64 * v + lane] = c[v];
+  };
   __syncthreads();
   // tile entry (i, j) of tile t
   auto at = [&](int t, int i, int j) -> double { return A[t * 256 + 64 * (i >> 2) + 16 * (i & 3) + j]; };
@@ -534,7 +597,7 @@ __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* _
     double a[4], m[4], pinv = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      a[q] = at(K * (K + 1) / 2 + K, lj, 4 * lc + q);
+      a[q] = at(place(K, K), lj, 4 * lc + q);
       m[q] = lj == 4 * lc + q ? 1.0 : 0.0;
     }
     bool ok = true;
@@ -545,7 +608,6 @@ __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* _
     for (int q = 0; q < 4; ++q) o[lj * CI_LD + 4 * lc + q] = m[q];
     if (lc == 0) o[16 * CI_LD + lj] = pinv;
   };
-  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
   auto mul = [&](const f64x4& a, const f64x4& b, f64x4 c) -> f64x4 {
 #pragma unroll
     for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
@@ -557,87 +619,157 @@ __global__ __launch_bounds__(CI_THREADS) void k_coarse_inverse(const ProbDesc* _
     for (int s = 0; s < 4; ++s) g[s] = X[lj * CI_LD + lc + 4 * s];
     return g;
   };
-  if (wave == 0) factor(0);
-  __syncthreads();
-  for (int K = 0; K < T; ++K) {
-    const double* M = sM + (K & 1) * CI_M;
-    const f64x4 Mr = rows(M);           // M[lj][lc + 4 s]
-    f64x4 Mc, ip;                       // M[lc + 4 s][lj], 1 / p[lc + 4 s]
+  auto blockM = [&](int K) -> const double* { return sM + (K & 1) * CI_M; };
+  auto tile = [&](int t) -> f64x4 {
+    f64x4 c;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      Mc[s] = M[(lc + 4 * s) * CI_LD + lj];
-      ip[s] = M[16 * CI_LD + lc + 4 * s];
+    for (int v = 0; v < 4; ++v) c[v] = A[t * 256 + 64 * v + lane];
+    return c;
+  };
+  // panel G' = G M^T, G = column K of the symmetric matrix; each wave turns
+  // its own tiles into rows through their places in the panel.  x: entries
+  // (lc + 4 v, lj) of the stored tile, (I, K) or (K, I)
+  auto panel = [&](int K, int I, const f64x4& x) {
+    double* X = G + 16 * I * CI_LD;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (I >= K)
+        X[(lc + 4 * v) * CI_LD + lj] = x[v];
+      else
+        X[lj * CI_LD + lc + 4 * v] = x[v];
     }
-    // panel G' = G M^T, G = column K of the symmetric matrix; each wave turns
-    // its own tiles into rows through their places in the panel
-    for (int I = wave; I < T; I += NW) {
-      const int t = I >= K ? I * (I + 1) / 2 + K : K * (K + 1) / 2 + I;
-      double* X = G + 16 * I * CI_LD;
+    TG_WAVE_SYNC();
+    const f64x4 g = mul(rows(X), rows(blockM(K)), zero);
+    TG_WAVE_SYNC();
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const double x = A[t * 256 + 64 * v + lane];   // entry (lc + 4 v, lj) of the stored tile
-        if (I >= K)
-          X[(lc + 4 * v) * CI_LD + lj] = x;
-        else
-          X[lj * CI_LD + lc + 4 * v] = x;
-      }
-      TG_WAVE_SYNC();
-      const f64x4 g = mul(rows(X), Mr, zero);
-      TG_WAVE_SYNC();
+    for (int v = 0; v < 4; ++v) X[(lc + 4 * v) * CI_LD + lj] = g[v];
+    const bool any = __any(!(x[0] == 0.0 && x[1] == 0.0 && x[2] == 0.0 && x[3] == 0.0));
+    if (lane == 0) sZ[I] = any;
+  };
+  // A tile whose row or column of the panel is zero keeps its value (zero itself
+  // in the pivot's row or column): beyond the band of the rows not yet swept,
+  // nearly a third of all updates at n = 288.
+  auto touched = [&](int K, int I, int J) -> bool {
+    return __builtin_amdgcn_readfirstlane((I == K || sZ[I]) && (J == K || sZ[J])) != 0;
+  };
+  // tile (I, J) after block pivot K, from its old value c
+  auto updated = [&](int K, int I, int J, const f64x4& c) -> f64x4 {
+    const double *M = blockM(K), *gi = G + 16 * I * CI_LD, *gj = G + 16 * J * CI_LD;
+    f64x4 ip;                               // 1 / p[lc + 4 s]
 #pragma unroll
-      for (int v = 0; v < 4; ++v) X[(lc + 4 * v) * CI_LD + lj] = g[v];
-    }
-    __syncthreads();
-    auto tile = [&](int t) -> f64x4 {
-      f64x4 c;
+    for (int s = 0; s < 4; ++s) ip[s] = M[16 * CI_LD + lc + 4 * s];
+    if (I != K && J != K) return mul(-rows(gi), rows(gj) * ip, c);   // A_IJ - G'_I diag(1/p) G'_J^T
+    f64x4 Mc;                               // M[lc + 4 s][lj]
 #pragma unroll
-      for (int v = 0; v < 4; ++v) c[v] = A[t * 256 + 64 * v + lane];
-      return c;
-    };
-    auto update = [&](int t, int I, int J, f64x4 c) {   // c: the tile's old value
-      const f64x4 gi = rows(G + 16 * I * CI_LD), gj = rows(G + 16 * J * CI_LD);
-      if (I != K && J != K) c = mul(-gi, gj * ip, c);   // A_IJ - G'_I diag(1/p) G'_J^T
-      else if (I != K) c = mul(gi * ip, Mc, zero);      // G'_I diag(1/p) M
-      else if (J != K) c = mul(Mc * ip, gj, zero);      // its transpose for a tile left of the diagonal
-      else c = -mul(Mc * ip, Mc, zero);                 // -M^T diag(1/p) M
-#pragma unroll
-      for (int v = 0; v < 4; ++v) A[t * 256 + 64 * v + lane] = c[v];
-    };
-    const int tn = (K + 1) * (K + 2) / 2 + K + 1;       // tile (K + 1, K + 1)
+    for (int s = 0; s < 4; ++s) Mc[s] = M[(lc + 4 * s) * CI_LD + lj];
+    if (I != K) return mul(rows(gi) * ip, Mc, zero);                 // G'_I diag(1/p) M
+    if (J != K) return mul(Mc * ip, rows(gj), zero);                 // its transpose for a tile left of the diagonal
+    return -mul(Mc * ip, Mc, zero);                                  // -M^T diag(1/p) M
+  };
+  // wave 0's part between two panels
+  auto next_pivot = [&](int K) {
+    if (K >= T) return;
+    put(place(K, K), updated(K - 1, K, K, tile(place(K, K))));
+    TG_WAVE_SYNC();                         // the tile is read back in another layout
+    factor(K);
+  };
+  if constexpr (FORM == CI_REG) {
+    // (the two roles' loops apart: wave 0 needs no room for tiles)
     if (wave == 0) {
-      if (K + 1 < T) {
-        update(tn, K + 1, K + 1, tile(tn));
-        TG_WAVE_SYNC();                                 // the tile is read back in another layout
-        factor(K + 1);
+      factor(0);
+      __syncthreads();
+      for (int K = 0; K < T; ++K) {
+        __syncthreads();
+        next_pivot(K + 1);
+        __syncthreads();
       }
     } else {
-      const int u0 = (wave - 1) * NT / (NW - 1), u1 = wave * NT / (NW - 1);
-      f64x4 next = zero;
-      int ij = 0, t = 0;
-      auto fetch = [&](int u) {   // the next tile's values are loaded one update ahead
-        ij = tile_of(u);
-        const int I = ij & 255;
-        t = I * (I + 1) / 2 + (ij >> 8);
-        next = tile(t);
-      };
-      if (u0 < u1) fetch(u0);
-      for (int u = u0; u < u1; ++u) {
-        const f64x4 c = next;
-        const int I = ij & 255, J = ij >> 8, tu = t;
-        if (u + 1 < u1) fetch(u + 1);
-        if (tu == tn) continue;                         // wave 0's
-        update(tu, I, J, c);
+      f64x4 R[CI_SLOTS];
+      int rij[CI_SLOTS];                    // this wave's register tiles, -1: none
+      ci_each<CI_SLOTS>([&](auto s) {
+        const int v = wave - 1 + (NW - 1) * s;
+        rij[s] = v < NR ? __builtin_amdgcn_readfirstlane(off_of(v)) : -1;
+        const int I = rij[s] & 255, t = rij[s] >= 0 ? I * (I + 1) / 2 + (rij[s] >> 8) : 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) R[s][q] = P.Cwork[t * 256 + 64 * q + lane];
+      });
+      __syncthreads();
+      for (int K = 0; K < T; ++K) {
+        ci_each<CI_SLOTS>([&](auto s) {
+          const int I = rij[s] & 255, J = rij[s] >> 8;
+          if (rij[s] >= 0 && (I == K || J == K)) panel(K, J == K ? I : J, R[s]);
+        });
+        for (int v = NR + wave - 1; v < NO; v += NW - 1) {
+          const int ij = __builtin_amdgcn_readfirstlane(off_of(v)), I = ij & 255, J = ij >> 8;
+          if (I == K || J == K) panel(K, J == K ? I : J, tile(T + v - NR));
+        }
+        __syncthreads();
+        ci_each<CI_SLOTS>([&](auto s) {
+          const int I = rij[s] & 255, J = rij[s] >> 8;
+          if (rij[s] >= 0 && touched(K, I, J)) R[s] = updated(K, I, J, R[s]);
+        });
+        for (int v = NR + wave - 1; v < NO; v += NW - 1) {
+          const int ij = __builtin_amdgcn_readfirstlane(off_of(v)), I = ij & 255, J = ij >> 8;
+          if (touched(K, I, J)) put(T + v - NR, updated(K, I, J, tile(T + v - NR)));
+        }
+        for (int I = NW - 1 - wave; I < T; I += NW - 1)
+          if (I != K + 1 && touched(K, I, I)) put(I, updated(K, I, I, tile(I)));
+        __syncthreads();
+      }
+      ci_each<CI_SLOTS>([&](auto s) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * (rij[s] & 255) + lc + 4 * v, c = 16 * (rij[s] >> 8) + lj;
+          if (rij[s] >= 0 && r < n && c < n) {
+            P.Cinv64[r * n + c] = P.Cinv64[c * n + r] = -R[s][v];
+            P.Cinv32[r * n + c] = P.Cinv32[c * n + r] = (float)-R[s][v];
+          }
+        }
+      });
+    }
+  } else {
+    if (wave == 0) factor(0);
+    __syncthreads();
+    for (int K = 0; K < T; ++K) {
+      for (int I = wave; I < T; I += NW) panel(K, I, tile(I >= K ? place(I, K) : place(K, I)));
+      __syncthreads();
+      if (wave == 0) {
+        next_pivot(K + 1);
+      } else {
+        const int u0 = (wave - 1) * NT / (NW - 1), u1 = wave * NT / (NW - 1);
+        f64x4 next = zero;
+        int ij = 0, t = 0;
+        auto fetch = [&](int u) {           // the next tile's values are loaded one update ahead
+          ij = tile_of(u);
+          t = place(ij & 255, ij >> 8);
+          next = tile(t);
+        };
+        if (u0 < u1) fetch(u0);
+        for (int u = u0; u < u1; ++u) {
+          const f64x4 c = next;
+          const int I = ij & 255, J = ij >> 8, tu = t;
+          if (u + 1 < u1) fetch(u + 1);
+          if ((I == K + 1 && J == K + 1) || !touched(K, I, J)) continue;   // (the former is wave 0's)
+          put(tu, updated(K, I, J, c));
+        }
+      }
+      __syncthreads();
+    }
+  }
+  for (int u = wave; u < NT; u += NW) {
+    const int ij = tile_of(u), I = ij & 255, J = ij >> 8, t = place(I, J);
+    if (FORM == CI_REG && I != J && t < T) continue;   // (held in registers)
+    const f64x4 c4 = tile(t);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * I + lc + 4 * v, c = 16 * J + lj;
+      // (a diagonal tile holds both triangles, equal up to rounding)
+      const double x = I == J ? -0.5 * (c4[v] + at(t, lj, lc + 4 * v)) : -c4[v];
+      if (r < n && c < n) {
+        P.Cinv64[r * n + c] = P.Cinv64[c * n + r] = x;
+        P.Cinv32[r * n + c] = P.Cinv32[c * n + r] = (float)x;
       }
     }
-    __syncthreads();
-  }
-  for (int q = threadIdx.x; q < n * n; q += CI_THREADS) {
-    const int r = max(q / n, q % n), c = min(q / n, q % n);
-    const int I = r >> 4, J = c >> 4, t = I * (I + 1) / 2 + J;
-    // (a diagonal tile holds both triangles, equal up to rounding)
-    const double v = I == J ? -0.5 * (at(t, r & 15, c & 15) + at(t, c & 15, r & 15)) : -at(t, r & 15, c & 15);
-    P.Cinv64[q] = v;
-    P.Cinv32[q] = (float)v;
   }
 }
 
@@ -1698,10 +1830,12 @@ static int coarse_lds_raise() {
   TG_HIP(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return fail(TG_EINVAL, "device index out of range");
   if (done[dev]) return TG_OK;
-  TG_HIP(hipFuncSetAttribute((const void*)k_coarse_inverse<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)(sizeof(double) * ci_lds_words(CI_LDS_N, true))));
-  TG_HIP(hipFuncSetAttribute((const void*)k_coarse_inverse<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)(sizeof(double) * ci_lds_words(TG_MAX_COARSE, false))));
+  const void* f[3] = {(const void*)k_coarse_inverse<CI_LDS>, (const void*)k_coarse_inverse<CI_REG>,
+                      (const void*)k_coarse_inverse<CI_MEM>};
+  const int nmax[3] = {CI_LDS_N, CI_REG_N, TG_MAX_COARSE};
+  for (int q = 0; q < 3; ++q)
+    TG_HIP(hipFuncSetAttribute(f[q], hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)(sizeof(double) * ci_lds_words(nmax[q], q))));
   done[dev] = true;
   return TG_OK;
 }
@@ -1727,22 +1861,25 @@ int k_set_density(Batch* b, hipStream_t s) {
       }
       w.end[u] = (int)blocks;
     }
+    for (int p : b->active) w.tiles = std::max(w.tiles, ci_tiles(b->grids[p]->ncoarse));
+    w.prob = b->prob.ptr;
+    blocks += (long long)b->prob.n * w.tiles;
     if (blocks) k_setup_tail<<<(unsigned)blocks, 256, 0, s>>>(b->desc_d, w);
     if (b->prob.n) {
       // which form inverts a problem's coarsest matrix depends only on its own
       // size, so a problem gets the same inverse alone or batched
-      int n_lds = 0, n_big = 0;
+      const int lim[4] = {0, CI_LDS_N, CI_REG_N, TG_MAX_COARSE};
+      int nmax[3] = {0, 0, 0};
       for (int p : b->active) {
         const int n = b->grids[p]->ncoarse;
-        if (n <= CI_LDS_N) n_lds = std::max(n_lds, n);
-        else n_big = std::max(n_big, n);
+        for (int q = 0; q < 3; ++q)
+          if (n > lim[q] && n <= lim[q + 1]) nmax[q] = std::max(nmax[q], n);
       }
-      if (n_lds)
-        k_coarse_inverse<true><<<nblk(b->prob), CI_THREADS, sizeof(double) * ci_lds_words(n_lds, true), s>>>(
-            b->desc_d, b->prob.ptr, bad, 1, CI_LDS_N);
-      if (n_big)
-        k_coarse_inverse<false><<<nblk(b->prob), CI_THREADS, sizeof(double) * ci_lds_words(n_big, false), s>>>(
-            b->desc_d, b->prob.ptr, bad, CI_LDS_N + 1, TG_MAX_COARSE);
+      for (int q = 0; q < 3; ++q)
+        if (nmax[q])
+          (q == CI_LDS ? k_coarse_inverse<CI_LDS> : q == CI_REG ? k_coarse_inverse<CI_REG> : k_coarse_inverse<CI_MEM>)
+              <<<nblk(b->prob), CI_THREADS, sizeof(double) * ci_lds_words(nmax[q], q), s>>>(
+                  b->desc_d, b->prob.ptr, bad, lim[q] + 1, lim[q + 1]);
     }
   });
   return check_launch("set_density kernels");
