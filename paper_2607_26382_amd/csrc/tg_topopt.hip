@@ -207,20 +207,27 @@ __global__ __launch_bounds__(TO_BLOCK) void k_max_change(const double* __restric
 // launch evaluates several midpoints at once, one set of workgroups per
 // midpoint, and the next launch (every workgroup for itself, from the
 // partial sums) takes the decisions, so nothing returns to the host on the
-// way.  With a bracket [l1, l2], l1 > 0, the midpoints are those of the next
-// `depth` levels of the bisection (2^depth - 1 of them).  While l1 = 0 the
+// way.  With a bracket [l1, l2], l1 > 0, whose ends' volumes are known, the
+// midpoints are those along the way to the multiplier that the two volumes
+// predict (the design goes as its inverse root, so that is where they are
+// interpolated): a launch takes as many halvings as the prediction is right
+// for, one more where it is not, and the nearer the ends the more of them.
+// Without the volumes (l2 as it was given) they are those of the next levels of
+// the bisection, 2^depth - 1 of them.  While l1 = 0 the
 // midpoints are l2 / 2, l2 / 4, ...: the volume does not increase with the
 // multiplier, so one that is not above the target decides every larger one,
 // and the midpoints are taken `stride` halvings apart until one is above.
 // The halvings, their order, the stop test and the midpoints are those of
 // one evaluation at a time; 64x32x32 took 31 us per halving with the volume
-// read back after each, 2.0 ms in all, now 0.2 ms.
+// read back after each, 2.0 ms in all; 14 launches with three levels of the
+// bisection in each, 0.20 ms; 7 or 8 with the prediction, 0.12 ms.
 constexpr int OC_MAX_CAND = 7;    // depth 3
 constexpr int OC_STRIDE = 6;
 constexpr int OC_MAX_HALVINGS = 200;
 struct OcState {
   double l1, l2, lm;
   double it, done, stride;        // halvings taken; stop test met; left-phase stride
+  double v1, v2;                  // volumes at l1 and l2 (NaN: not known)
 };
 constexpr int OC_STATE_W = 8;
 static_assert(sizeof(OcState) <= OC_STATE_W * sizeof(double), "state words");
@@ -228,14 +235,30 @@ static_assert(sizeof(OcState) <= OC_STATE_W * sizeof(double), "state words");
 __device__ __forceinline__ bool oc_more(const OcState& s) {
   return s.it < OC_MAX_HALVINGS && (s.l2 - s.l1) / (s.l1 + s.l2) > 1e-9;
 }
+// the multiplier that the volumes at the bracket's ends predict; 0: none
+__device__ __forceinline__ double oc_guess(const OcState& s, double target) {
+  if (s.l1 == 0.0 || !(s.v1 > s.v2)) return 0.0;
+  const double u1 = 1.0 / sqrt(s.l1), u2 = 1.0 / sqrt(s.l2);
+  const double u = u1 + (u2 - u1) * ((s.v1 - target) / (s.v1 - s.v2));
+  return 1.0 / (u * u);
+}
 // the c-th midpoint (c < nc) the launch after state s evaluates; 0: none
-__device__ __forceinline__ double oc_midpoint(const OcState& s, int c) {
+__device__ __forceinline__ double oc_midpoint(const OcState& s, int c, double target) {
   if (s.l1 == 0.0) {
     const double lev = s.stride * (c + 1);
     return s.it + lev <= OC_MAX_HALVINGS ? ldexp(s.l2, -(int)lev) : 0.0;
   }
-  // node c + 1 of the heap-ordered tree of halvings: its path from the top bit
   double l1 = s.l1, l2 = s.l2;
+  const double guess = oc_guess(s, target);
+  if (guess > 0.0) {
+    for (int q = 0; q < c; ++q) {
+      const double m = 0.5 * (l1 + l2);
+      if (guess > m) l1 = m;
+      else l2 = m;
+    }
+    return 0.5 * (l1 + l2);
+  }
+  // node c + 1 of the heap-ordered tree of halvings: its path from the top bit
   for (int b = 30 - __clz(c + 1); b >= 0; --b) {
     const double m = 0.5 * (l1 + l2);
     if ((c + 1) >> b & 1) l1 = m;
@@ -257,6 +280,7 @@ __device__ __forceinline__ OcState oc_advance(OcState s, const double* vol, int 
       if (vol[c] > target) {
         if (stride == 1) {
           s.l1 = s.lm = 0.5 * s.l2;
+          s.v1 = vol[c];
           s.it += 1.0;
         } else {
           s.stride = 1.0;         // within the next `stride` halvings
@@ -264,16 +288,20 @@ __device__ __forceinline__ OcState oc_advance(OcState s, const double* vol, int 
         break;
       }
       s.l2 = s.lm = ldexp(s.l2, -stride);
+      s.v2 = vol[c];
       s.it += stride;
     }
   } else {
+    const double guess = oc_guess(s, target);
     for (int c = 0; c < nc && oc_more(s);) {
       s.lm = 0.5 * (s.l1 + s.l2);
       s.it += 1.0;
       const bool above = vol[c] > target;
-      if (above) s.l1 = s.lm;
-      else s.l2 = s.lm;
-      c = 2 * c + 1 + (above ? 1 : 0);
+      if (above) s.l1 = s.lm, s.v1 = vol[c];
+      else s.l2 = s.lm, s.v2 = vol[c];
+      if (guess == 0.0) c = 2 * c + 1 + (above ? 1 : 0);
+      else if (above == (guess > s.lm)) ++c;
+      else break;
     }
   }
   if (!oc_more(s)) s.done = 1.0;
@@ -283,7 +311,7 @@ __device__ __forceinline__ OcState oc_advance(OcState s, const double* vol, int 
 // the state this launch starts from: the previous launch's state advanced by
 // its partial sums (prev NULL: the first launch), the same in every workgroup
 __device__ __forceinline__ OcState oc_state(const double* prev, int nb, int nc, double target, double* vol) {
-  if (!prev) return {0.0, 1e9, 0.5e9, 0.0, 0.0, (double)OC_STRIDE};
+  if (!prev) return {0.0, 1e9, 0.5e9, 0.0, 0.0, (double)OC_STRIDE, NAN, NAN};
   OcState s = *(const OcState*)prev;
   if (s.done != 0.0) return s;
   const int c = threadIdx.x >> 5, l = threadIdx.x & 31;
@@ -324,7 +352,7 @@ __global__ __launch_bounds__(TO_BLOCK) void k_oc_volumes(Hat h, Dims D, const do
   const OcState s = oc_state(prev, nb, nc, target, vol);
   if (blockIdx.x == 0 && c == 0 && threadIdx.x == 0) *(OcState*)next = s;
   if (s.done != 0.0) return;
-  const double lam = oc_midpoint(s, c);
+  const double lam = oc_midpoint(s, c, target);
   if (lam == 0.0) {
     if (threadIdx.x == 0) next[OC_STATE_W + c * nb + blockIdx.x] = 0.0;
     return;
@@ -458,8 +486,9 @@ int oc_update(const tg_grid* g, const double* x, const double* dc, const double*
   const double target = volfrac * (double)D.n * pr.den - (double)D.n * pr.t1;
   // Midpoints per launch: a launch costs about 7 us beside its work (its own
   // start and the previous launch's sums), and the work of one midpoint is
-  // about 1 us per 65,536 elements (14 us per launch of seven there), so three
-  // levels at once pay up to 2^18 elements and two up to 2^20.
+  // about 1 us per 65,536 elements (14 us per launch of seven there), so seven
+  // at once (some 8 launches, against 14 with three and 35 to 40 with one) pay up
+  // to 2^18 elements and three up to 2^20.
   const int nc = D.n <= (1 << 18) ? 7 : D.n <= (1 << 20) ? 3 : 1;
   // two buffers of one state and nc rows of partial sums each, and a state
   const long long cap = (long long)TG_PART_W * g->lv[0].n_chunks;
@@ -470,8 +499,9 @@ int oc_update(const tg_grid* g, const double* x, const double* dc, const double*
   TG_HIP(hipGetLastError());
   const double* prev = nullptr;
   int t = 0;
-  // 72 halvings' launches before the first look at the state, then some more
-  for (int more = nc == 7 ? 14 : nc == 3 ? 24 : 48;; more = 4) {
+  // the launches that most updates need before the first look at the state (7 or 8,
+  // 12 to 15, 33 to 42 over multipliers of 1e-12 to 1e6), then some more
+  for (int more = nc == 7 ? 8 : nc == 3 ? 15 : 42;; more = nc == 1 ? 6 : 3) {
     for (int q = 0; q < more; ++q, ++t) {
       double* next = buf[t & 1];
 #define TO_OC(R)                                                                                                    \
