@@ -1133,12 +1133,13 @@ template <> ModeCoef<double> mcoef<double>(const tg_grid* g) { return g->mc64; }
 template <> ModeCoef<float> mcoef<float>(const tg_grid* g) { return g->mc32; }
 
 // Tallest tile that the running problems take at level l, and whether the
-// first post-sweep there forms x + P e itself (FOP_SMOOTHP).  Up to 8 layers
+// first post-sweep there forms x + P e itself (FOP_SMOOTHP).  Up to 14 layers
 // its coarse nodes add at most 9 KB (FP32) of LDS to the 27 KB of the sweep;
-// taller tiles (full devices) would lose workgroups per CU, and keep the
-// separate pass.  At 64x32x32 (split BF16) the two prolongations took 4.4 us
-// and the sweeps after them 6.2 and 5.3, the prolonging sweeps take 8.7 and 7.9.
-#define FZ_SP_MAX 8
+// taller tiles would lose workgroups per CU, and keep the separate pass.  At
+// 64x32x32 (split BF16) the two prolongations took 4.4 us and the sweeps after them
+// 6.2 and 5.3, the prolonging sweeps take 8.7 and 7.9; 100 problems of 64x32x32 at
+// 11 layers: guarded policy 978 -> 970 ms, 24 of 96x48x48 at 13: 853 -> 845.
+#define FZ_SP_MAX 14
 static int fz_height(const Batch* b, int l) {
   int h = 0;
   for (int p : b->active)
