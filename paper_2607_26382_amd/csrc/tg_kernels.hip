@@ -2277,6 +2277,7 @@ int krylov_bind(const KrylovOne& K, hipStream_t s) {
   d.nlev = 1;
   d.small = K.small;
   d.part = K.part;
+  d.gate = K.status;   // a process that stopped (b = 0 among others) leaves its pool alone
   d.lv[0].n_nodes = (int)(K.n / 3);
   d.lv[0].n_chunks = K.chunks;
   d.lv[0].stride = K.stride;
@@ -2284,7 +2285,7 @@ int krylov_bind(const KrylovOne& K, hipStream_t s) {
   k_kry_bind_<<<std::min(64, K.q + 2), 256, 0, s>>>(d, K.desc, K.list, K.chunks, K.q + 2);
   return check_launch("krylov bind");
 }
-// V_0 = src and the chunk sums of src . src
+// V_0 = src (its tail cleared) and the chunk sums of src . src
 __global__ __launch_bounds__(256) void k_kry_start_(const ProbDesc* __restrict__ probs, const double* src) {
   __shared__ double sh[4];
   const ProbDesc& P = *probs;
@@ -2300,6 +2301,8 @@ __global__ __launch_bounds__(256) void k_kry_start_(const ProbDesc* __restrict__
       const double x = src[i];
       if (v != src) v[i] = x;
       a += x * x;
+    } else {
+      v[i] = 0.0;
     }
   }
   a = block_sum256(a, sh);
