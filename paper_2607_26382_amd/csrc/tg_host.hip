@@ -236,6 +236,7 @@ int batch_init(Batch* b, int n, tg_grid* const* grids) {
   }
   b->sc_h.assign(n + 8, 0.0);
   b->host_desc.resize(n);
+  b->desc_rev.assign(n, 0);
   batch_choose_zc(b);
   return TG_OK;
 }
@@ -245,6 +246,7 @@ int batch_bind(Batch* b, void* ws, size_t bytes) {
   if (!ws || bytes < need) return fail(TG_EWORKSPACE, "batch workspace too small");
   Bump bp(ws, bytes, false);
   b->lists_valid = false;
+  b->desc_rev.assign(b->n, 0);
   drop_graphs(b);
   batch_layout(bp, b, b->n, list_capacity(b->grids));
   b->ws = ws;
@@ -285,6 +287,7 @@ unsigned long long batch_zc_hash(const Batch* b) {
 int batch_upload_desc(Batch* b, hipStream_t s) {
   for (int p = 0; p < b->n; ++p) {
     b->host_desc[p] = b->grids[p]->desc;
+    b->desc_rev[p] = b->grids[p]->desc_rev;
     b->host_desc[p].gate = b->gated ? b->sc_d + p : nullptr;
     const size_t lim = vbottom_lds_limit();
     b->host_desc[p].vb_lb32 = vbottom_level(b->grids[p], sizeof(float), lim);
@@ -307,7 +310,14 @@ int batch_set_active(Batch* b, const std::vector<int>& active, hipStream_t s, bo
   {
     int cap[TG_MAXLEV];
     batch_tile_caps(b, active, cap);
-    if (!std::equal(cap, cap + TG_MAXLEV, b->zc_cap)) {
+    // (a grid may have been bound or given its density through another batch)
+    bool stale = false;
+    for (int p = 0; p < b->n; ++p) {
+      if (b->grids[p]->mmax != b->grids[0]->mmax)
+        return fail(TG_EINVAL, "grids of one batch must be bound with the same max_restart");
+      stale = stale || b->desc_rev[p] != b->grids[p]->desc_rev;
+    }
+    if (stale || !std::equal(cap, cap + TG_MAXLEV, b->zc_cap)) {
       // the descriptors carry the tile heights the kernels use
       std::copy(cap, cap + TG_MAXLEV, b->zc_cap);
       const int rc = batch_upload_desc(b, s);
@@ -543,6 +553,7 @@ int grid_bind(tg_grid* g, void* ws, size_t bytes, int mmax) {
   g->ws = ws;
   g->ws_bytes = bytes;
   g->bound = true;
+  ++g->desc_rev;
   g->density_set = false;
   // constant tables
   float ke32[576];

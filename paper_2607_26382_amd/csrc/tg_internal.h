@@ -209,6 +209,7 @@ struct tg_grid {
   int cap = 0;
   tg::SmallLayout sl;
   tg::ProbDesc desc;          // host copy of this grid's device descriptor
+  unsigned desc_rev = 0;      // changes of desc (binding, density) that every batch of the grid has to upload
   bool bound = false;
   bool density_set = false;
   bool numeric_bad = false;   // coarsest factorization met a non-positive pivot
@@ -251,6 +252,7 @@ struct Batch {
   bool vb_need[2][TG_MAXLEV] = {};
   std::vector<int2> host_lists;   // kept alive until the next synchronization
   std::vector<ProbDesc> host_desc;
+  std::vector<unsigned> desc_rev; // the grids' desc_rev that desc_d holds
   int zc[TG_MAXLEV] = {};         // z-tile height per level for this batch
   // caps on the heights while only part of the batch runs (batch_set_active)
   int zc_cap[TG_MAXLEV] = {1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30};

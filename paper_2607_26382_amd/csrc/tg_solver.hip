@@ -30,6 +30,7 @@ int set_density_batch(Batch* b, const std::vector<int>& which, const double* con
     tg_grid* g = b->grids[i];
     g->desc.ext0 = rho_d[q];
     g->desc.rho_min = rho_min[q];
+    ++g->desc_rev;
     g->p = p;
     g->rho_min = rho_min[q];
   }
