@@ -90,6 +90,7 @@ bool autotune_lookup(Batch* b, int prec) {
   const std::vector<int>& v = it->second;
   for (int l = 0; l < TG_MAXLEV; ++l)
     if (v[l] > 0) b->zc[l] = v[l];
+  b->tuned = true;
   b->zc_size.clear();
   const auto sizes = batch_sizes(b);
   if (sizes.size() > 1 && v.size() == (sizes.size() + 1) * TG_MAXLEV)
@@ -112,6 +113,7 @@ int autotune_batch(Batch* b, int prec, hipStream_t s, double* best_us, bool forc
   TG_HIP(hipEventCreate(&e1));
   int rc = TG_OK;
   b->zc_size.clear();
+  b->tuned = true;
   const int mf = prec == TG_BF16MFMA ? 1 : prec == TG_BF16X3MFMA ? 2 : 0;
   // time of the level-l smoothing sweep over the whole batch with the
   // current heights (microseconds, mean of 3 after one untimed sweep)

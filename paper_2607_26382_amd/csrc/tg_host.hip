@@ -299,11 +299,26 @@ int batch_upload_desc(Batch* b, hipStream_t s) {
   return TG_OK;
 }
 
-// z-tile caps for a subset of the batch (the tail of a ladder): the height the
-// rule gives the problems that run, which is lower where fewer of them do.
-// Results do not depend on the heights.
+// z-tile caps for a subset of the batch (the tail of a ladder).  Heights that
+// zm_rule chose give way to the rule's for the problems that run, which are lower
+// where fewer of them do.  Heights that the autotuner measured stay while the
+// running problems still give 1024 tiles at them (four per CU: the device is
+// filled as it was when they were measured).  Below that the rule's serve better
+// than the tallest of a few that restore 1024: 64 problems of four sizes 73.9 and
+// 74.6 ms, the policy of 24 64x32x32 states 296.2 and 298.1 ms.  Results do not depend on
+// the heights.
 static void batch_tile_caps(const Batch* b, const std::vector<int>& active, int* cap) {
-  for (int l = 0; l < TG_MAXLEV; ++l) cap[l] = (int)active.size() >= b->n ? 1 << 30 : zm_rule(b, active, l);
+  for (int l = 0; l < TG_MAXLEV; ++l) {
+    cap[l] = 1 << 30;
+    if ((int)active.size() >= b->n) continue;
+    if (b->tuned) {
+      long long t = 0;
+      for (int p : active)
+        if (l < b->grids[p]->nlev - 1) t += zm_tiles(b->grids[p], l, batch_zc(b, p, l));
+      if (t >= 1024) continue;
+    }
+    cap[l] = zm_rule(b, active, l);
+  }
 }
 
 int batch_set_active(Batch* b, const std::vector<int>& active, hipStream_t s, bool with_elem) {
