@@ -385,18 +385,26 @@ struct FzX {
   T om2, beta;
 };
 struct FzNone {};
+// FOP_APPLY of a lone problem (zc > 0): tiles of zc layers, numbered by workgroup,
+// in place of the work list and the descriptor's height
+struct FzOp {
+  int zc;
+};
 // (a member type: a kernel's signature must not spell out an enumerator of the
 // unnamed enum, whose mangled number differs between the host and device passes)
 template <class T, int OP>
 struct FzArgOf {
-  typedef std::conditional_t<(OP >= FOP_APPLYJ), FzX<T>, FzNone> type;
+  typedef std::conditional_t<(OP >= FOP_APPLYJ), FzX<T>, std::conditional_t<OP == FOP_APPLY, FzOp, FzNone>> type;
 };
 template <class T, int OP>
 using FzArg = typename FzArgOf<T, OP>::type;
 template <class T>
 __device__ inline FzX<T> fz_x(const FzX<T>& a) { return a; }
-template <class T>
-__device__ inline FzX<T> fz_x(const FzNone&) { return {}; }
+template <class T, class A>
+__device__ inline FzX<T> fz_x(const A&) { return {}; }
+__device__ inline int fz_lone(const FzOp& a) { return a.zc; }
+template <class A>
+__device__ inline int fz_lone(const A&) { return 0; }
 
 // KIND 0: fine level, element = E_e Ke; KIND 1: level 1, matrix-free Galerkin
 // (moment form); KIND 2 / 3: fine level with the BF16 matrix-core contraction
@@ -432,7 +440,8 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
   T* sc = (T*)fz_smem;
   constexpr bool SP = (OP == FOP_SMOOTHP || OP == FOP_SMOOTHPX);
   MfmaA mfA;
-  const int2 wi = work[xcd_tile(blockIdx.x, gridDim.x)];
+  const int lone = fz_lone(fxa), wt = xcd_tile(blockIdx.x, gridDim.x);
+  const int2 wi = lone ? make_int2(0, wt) : work[wt];
   const ProbDesc& P = probs[wi.x];
   TG_GATE(P);
   // inside a V-cycle, levels from the problem's bottom level down belong to k_vbottom
@@ -448,7 +457,7 @@ __global__ __launch_bounds__(256) void k_fine_zm(const ProbDesc* __restrict__ pr
   const int ntx = RST ? (NXc + RZ_C - 1) / RZ_C : (NX + FZ_OUT - 1) / FZ_OUT;
   const int nty = RST ? (NYc + RZ_C - 1) / RZ_C : (NY + FZ_OUT - 1) / FZ_OUT;
   const int tile = wi.y;
-  const int zc = L.zc;
+  const int zc = lone ? lone : L.zc;
   const int tiz = tile / (ntx * nty), rem = tile - tiz * ntx * nty;
   const int tiy = rem / ntx, tix = rem - tiy * ntx;
   const int x0 = RST ? 2 * RZ_C * tix - 1 : tix * FZ_OUT;
@@ -1122,10 +1131,50 @@ int zm_rule(const Batch* b, const std::vector<int>& which, int l) {
   return (int)std::min<long long>(6, std::max<long long>(1, (tiles(1) + 767) / 768));
 }
 
+// z-tile height of the operator on a lone grid, per arithmetic (0: FP64, 1: FP32,
+// 2: matrix cores): the height h that makes (h + start) t[k] least, k the tiles that
+// the fullest CU holds.  t is a layer's time with 1, 2, 3 and 4 tiles on a CU, and per tile
+// beyond, relative to one alone, start the layers' worth of time before a tile's first;
+// both fitted to the operator at twelve heights on 37 grids of 1 k to 4 M elements (4 %
+// rms), where the heights so chosen are within 1 % of the best measured on average.  The
+// sweeps' heights (zm_rule), chosen for FP64 and the other forms alike, cost the operator up
+// to a fifth: 167x76x63, FP64 / FP32 / split, 6 layers 22.8 / 13.1 / 19.3 us, with its own 19.8 / 12.1 /
+// 17.9; 74x44x45 BF16 8.6 and 7.0; 223x82x85 FP64 29.8 and 27.2.
+static int op_height(const tg_grid* g, int form) {
+  static const double model[3][6] = {   // t[1..4], per tile beyond, start
+      {1.0, 1.46, 1.93, 2.69, 0.60, 1.6}, {1.0, 1.20, 1.51, 1.90, 0.41, 1.7}, {1.0, 1.40, 1.82, 2.30, 0.45, 3.0}};
+  const double* m = model[form];
+  const int NZ = g->lv[0].ez + 1;
+  int best = 1;
+  double least = 1e300;
+  for (int h = 1; h <= NZ; ++h) {
+    const int k = (zm_tiles(g, 0, h) + 255) / 256;
+    const double c = (zm_height(NZ, h) + m[5]) * (k <= 4 ? m[k - 1] : m[3] + m[4] * (k - 4));
+    if (c < least) least = c, best = h;
+  }
+  return best;
+}
+
 void batch_choose_zc(Batch* b) {
   std::vector<int> all(b->n);
   for (int i = 0; i < b->n; ++i) all[i] = i;
   for (int l = 0; l < TG_MAXLEV; ++l) b->zc[l] = zm_rule(b, all, l);
+  for (int q = 0; q < 3; ++q) b->op_zc[q] = b->n == 1 ? op_height(b->grids[0], q) : 0;
+}
+
+// y = K x of a batch of one at heights of its own (slots or external vectors)
+int launch_op_lone(const Batch* b, int prec, int sx, const void* ex, int sy, void* ey, hipStream_t s) {
+  const tg_grid* g = b->grids[0];
+  const int zc = b->op_zc[prec < TG_BF16MFMA ? prec : 2], n = zm_tiles(g, 0, zc);
+  const FzOp op = {zm_height(g->lv[0].ez + 1, zc)};
+#define TG_LONE(T, KV, MC) \
+  k_fine_zm<T, FOP_APPLY, KV><<<n, 256, 0, s>>>(b->desc_d, nullptr, 0, sx, ex, -1, nullptr, sy, ey, -1, T(0), MC, 0, op)
+  if (prec == TG_F64) TG_LONE(double, 0, g->mc64);
+  else if (prec == TG_F32) TG_LONE(float, 0, g->mc32);
+  else if (prec == TG_BF16MFMA) TG_LONE(float, 2, g->mc32);
+  else TG_LONE(float, 3, g->mc32);
+#undef TG_LONE
+  return TG_OK;
 }
 
 template <class T> static ModeCoef<T> mcoef(const tg_grid* g);

@@ -254,6 +254,7 @@ struct Batch {
   std::vector<ProbDesc> host_desc;
   std::vector<unsigned> desc_rev; // the grids' desc_rev that desc_d holds
   int zc[TG_MAXLEV] = {};         // z-tile height per level for this batch
+  int op_zc[3] = {};              // heights of a lone problem's operator (launch_op_lone), 0: the list's
   bool tuned = false;             // zc and zc_size come from the autotuner, not from zm_rule
   // caps on the heights while only part of the batch runs (batch_set_active)
   int zc_cap[TG_MAXLEV] = {1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30};
@@ -387,6 +388,7 @@ template <class T>
 // from zero into slot sy2
 int launch_fine(const Batch* b, const DevList& dl, int l, int op, int sx, const void* ex, int sb,
                 const void* eb, int sy, void* ey, double omega, hipStream_t s, int sy2 = -1, int vbskip = 0);
+int launch_op_lone(const Batch* b, int prec, int sx, const void* ex, int sy, void* ey, hipStream_t s);
 // whether level l's first post-sweep takes the prolongation in (op 6, sy2 = the
 // next level's slot)
 bool fine_prolongs(const Batch* b, int l);

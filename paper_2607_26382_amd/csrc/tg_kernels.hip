@@ -1905,7 +1905,12 @@ static double op_bytes(const Batch* b, int l, int lmode, int op) {
 }
 
 int k_apply(Batch* b, int prec, int sx, const void* ex, int sy, void* ey, hipStream_t s) {
-  if (prec == TG_BF16MFMA || prec == TG_BF16X3MFMA)
+  // (measured heights serve the operator as well)
+  if (b->op_zc[0] && !b->tuned && !b->active.empty())
+    TG_TIMED(prec == TG_F64 ? TG_KT_APPLY_F64 : TG_KT_VCYCLE_FINE,
+             (prec == TG_F64 ? op_bytes<double>(b, 0, 0, OP_APPLY) : op_bytes<float>(b, 0, 0, OP_APPLY)),
+             launch_op_lone(b, prec, sx, ex, sy, ey, s));
+  else if (prec == TG_BF16MFMA || prec == TG_BF16X3MFMA)
     TG_TIMED(TG_KT_VCYCLE_FINE, (op_bytes<float>(b, 0, 0, OP_APPLY)),
              launch_fine_mfma(b, b->fine, OP_APPLY, prec == TG_BF16X3MFMA, sx, ex, 0, nullptr, sy, ey, 0.0,
                               false, s));
