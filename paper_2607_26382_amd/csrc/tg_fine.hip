@@ -1287,6 +1287,7 @@ template int launch_fine<float>(const Batch*, const DevList&, int, int, int, con
                                 int, void*, double, hipStream_t, int, int);
 
 // Level primitives of host-stepped cycles (FP64, external vectors of level l).
+// FOP_APPLYJ is a form of the finest level only, FOP_SMOOTHPX of the others.
 template <int OP>
 static void launch_x64(const Batch* b, const DevList& dl, int l, const double* x, const double* bb, double* y,
                        double omega, const FzX<double>& fx, size_t dyn, hipStream_t s) {
@@ -1294,9 +1295,12 @@ static void launch_x64(const Batch* b, const DevList& dl, int l, const double* x
   const ModeCoef<double> mc = mcoef<double>(b->grids[0]);
 #define TG_X64(KV) \
   k_fine_zm<double, OP, KV><<<dl.n, 256, dyn, s>>>(b->desc_d, dl.ptr, l, -1, x, -1, bb, -1, y, -1, omega, mc, 0, fx)
-  if (l == 0) TG_X64(0);
-  else if (l <= TG_MF_LEVELS) TG_X64(1);
-  else TG_X64(4);
+  if (l == 0) {
+    if constexpr (OP != FOP_SMOOTHPX) TG_X64(0);
+  } else if constexpr (OP != FOP_APPLYJ) {
+    if (l <= TG_MF_LEVELS) TG_X64(1);
+    else TG_X64(4);
+  }
 #undef TG_X64
 }
 // z = D^-1 (*scale bb), y = K z (finest level)
