@@ -1131,25 +1131,33 @@ int zm_rule(const Batch* b, const std::vector<int>& which, int l) {
   return (int)std::min<long long>(6, std::max<long long>(1, (tiles(1) + 767) / 768));
 }
 
-// z-tile height of the operator on a lone grid, per arithmetic (0: FP64, 1: FP32,
-// 2: matrix cores): the height h that makes (h + start) t[k] least, k the tiles that
-// the fullest CU holds.  t is a layer's time with 1, 2, 3 and 4 tiles on a CU, and per tile
-// beyond, relative to one alone, start the layers' worth of time before a tile's first;
-// both fitted to the operator at twelve heights on 37 grids of 1 k to 4 M elements (4 %
-// rms), where the heights so chosen are within 1 % of the best measured on average.  The
-// sweeps' heights (zm_rule), chosen for FP64 and the other forms alike, cost the operator up
-// to a fifth: 167x76x63, FP64 / FP32 / split, 6 layers 22.8 / 13.1 / 19.3 us, with its own 19.8 / 12.1 /
-// 17.9; 74x44x45 BF16 8.6 and 7.0; 223x82x85 FP64 29.8 and 27.2.
-static int op_height(const tg_grid* g, int form) {
-  static const double model[3][6] = {   // t[1..4], per tile beyond, start
-      {1.0, 1.46, 1.93, 2.69, 0.60, 1.6}, {1.0, 1.20, 1.51, 1.90, 0.41, 1.7}, {1.0, 1.40, 1.82, 2.30, 0.45, 3.0}};
-  const double* m = model[form];
+// z-tile height of the operator on a lone grid, per arithmetic: the height h that
+// makes (h + start) T(k) least, k the tiles of the fullest CU.  t[r - 1] is a layer's
+// time with r tiles resident on a CU, relative to one alone; as many fit as t has
+// entries (registers), so k of them take whole rounds of t's last and the rest.
+// `start` is a tile's time before its first layer, in layers.  Fitted to the operator
+// at eleven heights on 25 grids of 1 k to 4 M elements (4 % rms); the heights so chosen
+// are within 1 % of the best measured on average, in each arithmetic.  The sweeps' heights
+// (zm_rule), one for all arithmetics, cost the operator up to a fifth: 167x76x63, FP64 /
+// FP32 / split, 6 layers 23.3 / 13.4 / 20.3 us, with its own 20.3 / 12.5 / 19.1; 99x68x44 BF16 11.0 and
+// 10.1; 203x124x84 split 33.9 and 29.9; 256x128x128 FP32, FP64 at 22 layers 38.9, 77.8, FP64 at 15 70.0.
+static int op_height(const tg_grid* g, int prec) {
+  struct Model {
+    int resident;
+    double t[5], start;
+  };
+  static const Model model[4] = {{3, {1.0, 1.45, 1.95}, 1.2},                // TG_F64
+                                 {5, {1.0, 1.20, 1.51, 1.88, 2.22}, 1.3},    // TG_F32
+                                 {5, {1.0, 1.40, 1.84, 2.28, 2.63}, 3.2},    // TG_BF16MFMA
+                                 {4, {1.0, 1.38, 1.81, 2.14}, 3.0}};         // TG_BF16X3MFMA
+  const Model& m = model[prec];
   const int NZ = g->lv[0].ez + 1;
   int best = 1;
   double least = 1e300;
   for (int h = 1; h <= NZ; ++h) {
-    const int k = (zm_tiles(g, 0, h) + 255) / 256;
-    const double c = (zm_height(NZ, h) + m[5]) * (k <= 4 ? m[k - 1] : m[3] + m[4] * (k - 4));
+    const int k = (zm_tiles(g, 0, h) + 255) / 256, rest = k % m.resident;
+    const double T = (k / m.resident) * m.t[m.resident - 1] + (rest ? m.t[rest - 1] : 0.0);
+    const double c = (zm_height(NZ, h) + m.start) * T;
     if (c < least) least = c, best = h;
   }
   return best;
@@ -1159,13 +1167,13 @@ void batch_choose_zc(Batch* b) {
   std::vector<int> all(b->n);
   for (int i = 0; i < b->n; ++i) all[i] = i;
   for (int l = 0; l < TG_MAXLEV; ++l) b->zc[l] = zm_rule(b, all, l);
-  for (int q = 0; q < 3; ++q) b->op_zc[q] = b->n == 1 ? op_height(b->grids[0], q) : 0;
+  for (int q = 0; q < 4; ++q) b->op_zc[q] = b->n == 1 ? op_height(b->grids[0], q) : 0;
 }
 
 // y = K x of a batch of one at heights of its own (slots or external vectors)
 int launch_op_lone(const Batch* b, int prec, int sx, const void* ex, int sy, void* ey, hipStream_t s) {
   const tg_grid* g = b->grids[0];
-  const int zc = b->op_zc[prec < TG_BF16MFMA ? prec : 2], n = zm_tiles(g, 0, zc);
+  const int zc = b->op_zc[prec], n = zm_tiles(g, 0, zc);
   const FzOp op = {zm_height(g->lv[0].ez + 1, zc)};
 #define TG_LONE(T, KV, MC) \
   k_fine_zm<T, FOP_APPLY, KV><<<n, 256, 0, s>>>(b->desc_d, nullptr, 0, sx, ex, -1, nullptr, sy, ey, -1, T(0), MC, 0, op)

@@ -254,7 +254,7 @@ struct Batch {
   std::vector<ProbDesc> host_desc;
   std::vector<unsigned> desc_rev; // the grids' desc_rev that desc_d holds
   int zc[TG_MAXLEV] = {};         // z-tile height per level for this batch
-  int op_zc[3] = {};              // heights of a lone problem's operator (launch_op_lone), 0: the list's
+  int op_zc[4] = {};              // heights of a lone problem's operator per precision (launch_op_lone), 0: the list's
   bool tuned = false;             // zc and zc_size come from the autotuner, not from zm_rule
   // caps on the heights while only part of the batch runs (batch_set_active)
   int zc_cap[TG_MAXLEV] = {1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30, 1 << 30};
