@@ -42,12 +42,12 @@ sys.path.insert(0, ROOT)
 # the listed kernel definitions within a file), else the traffic is reported
 # as null.
 MEASURED_TRAFFIC = {
-    "vcycle_fine_op": {"bytes_per_launch": 220.0e6, "sources": {"tg_fine.hip:k_fine_zm": "19467845af83fd66"},
+    "vcycle_fine_op": {"bytes_per_launch": 221.3e6, "sources": {"tg_fine.hip:k_fine_zm": "7265d3304b2da632"},
                        "profile": "profiles/policy_severe102_64x32x32_hbm_counters.md"},
-    "multidot": {"bytes_per_launch": 1728.5e6, "sources": {"tg_kernels.hip:k_dots2_": "4a3f94abdb36d47c",
+    "multidot": {"bytes_per_launch": 1727.8e6, "sources": {"tg_kernels.hip:k_dots2_": "958fba021d12b294",
                                                            "tg_kernels.hip:k_multidot_": "2ecbcc0448c99c92"},
                  "profile": "profiles/policy_severe102_64x32x32_hbm_counters.md"},
-    "vector_update": {"bytes_per_launch": 1920.4e6, "sources": {"tg_kernels.hip:k_update2_": "eb211e836eb4dda9",
+    "vector_update": {"bytes_per_launch": 1920.1e6, "sources": {"tg_kernels.hip:k_update2_": "5414d15817ba7216",
                                                                 "tg_kernels.hip:k_xupdate_": "0fc098785e738a14"},
                       "profile": "profiles/policy_severe102_64x32x32_hbm_counters.md"},
 }

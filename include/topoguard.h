@@ -404,7 +404,8 @@ int tg_batch_select_floor(tg_batch* b, const double* const* rho_d, const double*
  * microseconds (-1 where nothing was timed).  Choices are cached per batch
  * signature (grid sizes in order, precision) for the process and, if the
  * environment variable TG_AUTOTUNE_CACHE names a file, across runs; a cached
- * choice is applied without timing unless force is nonzero.  Tile heights
+ * choice is applied without timing unless force is nonzero.  While only part of
+ * the batch runs, the choices stay where they still give 1024 tiles.  Tile heights
  * change only the work decomposition: results agree with untuned runs to
  * rounding.  Synchronises the stream; TG_ESTATE before set_density. */
 int tg_batch_autotune(tg_batch* b, int prec, int force, int* zc_out, double* us_out, void* stream);

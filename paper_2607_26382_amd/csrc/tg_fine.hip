@@ -1107,12 +1107,12 @@ int rz_tiles(const tg_grid* g, int l, int zmax) {
 // recomputes one element layer, so taller tiles do less redundant work, but a
 // tile marches its layers one after the other (about 1 us each while the
 // device is not full).  Up to 768 tiles (three per CU) the march is what
-// counts: the lowest height that does not exceed that, at most 6.  Beyond, the
-// tallest of 16, 12 and 8 that still gives 2048 tiles, and 24 on grids of at
-// least 64 node layers from 768 tiles on.  Measured V-cycles, at heights of at
-// least 4 before and so now: 69 -> 59 us (16x8x8 FP64), 159 -> 129 (64x32x32
-// split BF16), 417 -> 300 (128x64x64 FP64); a 256x128x128 sweep 84 -> 68 us
-// from 8 layers to 22.
+// counts: the lowest height that gives about that many (the balanced heights may
+// give some more), at most 6.  Beyond, the tallest of 16, 12 and 8 that still gives
+// 2048 tiles, and 24 on grids of at least 64 node layers from 768 tiles on.  The
+// limits rest on these V-cycles, at heights of at least 4 before and so after:
+// 166 -> 136 us (64x32x32 split BF16), 451 -> 334 (128x64x64 FP64), a plain solve of 16x8x8
+// 2113 -> 1757, and on a 256x128x128 sweep, 84 us at 8 layers and 68 at 22.
 int zm_rule(const Batch* b, const std::vector<int>& which, int l) {
   int nz_min = INT_MAX;
   auto tiles = [&](int c) {
@@ -1191,11 +1191,13 @@ template <> ModeCoef<float> mcoef<float>(const tg_grid* g) { return g->mc32; }
 
 // Tallest tile that the running problems take at level l, and whether the
 // first post-sweep there forms x + P e itself (FOP_SMOOTHP).  Up to 14 layers
-// its coarse nodes add at most 9 KB (FP32) of LDS to the 27 KB of the sweep;
-// taller tiles would lose workgroups per CU, and keep the separate pass.  At
-// 64x32x32 (split BF16) the two prolongations took 4.4 us and the sweeps after them
-// 6.2 and 5.3, the prolonging sweeps take 8.7 and 7.9; 100 problems of 64x32x32 at
-// 11 layers: guarded policy 978 -> 970 ms, 24 of 96x48x48 at 13: 853 -> 845.
+// its coarse nodes add at most 12 KB (FP32) or 24 KB (FP64) of LDS to the sweep's 27
+// or 31.5, so that the workgroups that its registers allow on a CU (four, two)
+// still fit; taller tiles keep the separate pass.  At 64x32x32 (split BF16) the two
+// prolongations took 4.4 us and the sweeps after them 6.2 and 5.3, the prolonging sweeps
+// take 8.7 and 7.9.  240 problems of 48x24x24 at 13 layers, twenty iterations in FP64 /
+// FP32 / split: 53.4 / 39.6 / 40.4 ms with the pass, 52.1 / 38.7 / 39.3 with the prolonging
+// sweep; 180 of 16x16x40 at 14 layers take the same either way.
 #define FZ_SP_MAX 14
 static int fz_height(const Batch* b, int l) {
   int h = 0;
@@ -1355,7 +1357,6 @@ int level_cheb_prolong64(const Batch* b, int l, const double* x, const double* e
 // the first sweep x = w D^-1 b of level lb in slots C_B and C_XA (written by
 // the restriction from level lb - 1; b only when lb is the coarsest level);
 // exit: the level-lb result in slot sfin.
-// threads per workgroup: FP32 fits 128 registers (16 waves), FP64 takes 256
 // threads per workgroup (FP32 fits 128 registers with 16 waves, FP64 takes
 // 256 with 8) and pieces of a stored element matrix in flight per group of
 // loads (measured: all 38 FP32 pieces at once with 512 threads is no faster)
@@ -1370,7 +1371,8 @@ struct VbThreads {
 // bottom's matrices (0.6 MB for a 16x8x8 level) out of the L2 cache, and one CU
 // gets them back slowly.  us per iteration with 0 / 2 / 4 / 8 helpers: 64x32x32
 // split 182.6 / 180.6 / 180.1 / 180.4, FP64 211.3 / 209.3 / 208.5 / 208.1; with the
-// matrices in the cache (cycles alone, 16x8x8) no difference.
+// matrices in the cache (cycles alone, 16x8x8) no difference.  With four, the trace has the
+// bottom of 64x32x32 split at 45 us inside a solve and at 54 in cycles back to back.
 constexpr int VB_HELPERS = 4, VB_CUS = 256;
 
 // LDS words (of type T) the bottom needs from level lb of grid g down

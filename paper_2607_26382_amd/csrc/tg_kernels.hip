@@ -497,9 +497,10 @@ __device__ __forceinline__ void ldl_block(double* a, double* m, int lane, double
 // pivot per barrier took 170 us at n = 108, and the global-memory Cholesky that
 // n > 141 used took 22.9 ms at n = 288; this form takes 38 and 244 us (47 and 322
 // with the matrix assembled by the one workgroup and no tile skipped).
-// Where the tiles are: in LDS up to CI_LDS_N, where all fit beside the panel; up
-// to CI_REG_N most of those left of the diagonal in registers, 8 a wave, the rest
-// in LDS; beyond, in the problem's work array, which one workgroup's waves keep in
+// Where the tiles are: all in LDS, beside the panel, up to CI_LDS_N (ten tile rows,
+// 141 KB, would fit too; at 150 unknowns the next form takes the same time: set-up of
+// 4x8x8 103.5 us either way); up to CI_REG_N most of those left of the diagonal in
+// registers, 8 a wave, the rest in LDS; beyond, in the problem's work array, which one workgroup's waves keep in
 // cache (n = 288 that way: 265 us).
 // Lane layouts of v_mfma_f64_16x16x4 (measured on gfx950): A[i][k] and
 // B[k][j] at lane i (j) + 16 k; D[i][j] at lane 16 (i % 4) + j, element i / 4.
